@@ -225,7 +225,7 @@ __device__ __forceinline__ typename Quad<ST>::V load_row(const void *__restrict_
     return Quad<ST>::load_buffer(r, lane_boff);
 }
 
-constexpr int kEntryBatch = 8;  // most state rows in flight per batch
+constexpr int kEntryBatch = 4;  // most state rows in flight per batch
 
 // Loads the state quads of the N entries (node, mult) at e, all before the
 // first use, and hands each to f with its multiplier.
@@ -249,11 +249,7 @@ __device__ __forceinline__ void walk_entries(cint32_t *e, int n_e, const void *_
         case 1: entry_batch<1, ST>(e, states, vstride, lane_boff, f); break;
         case 2: entry_batch<2, ST>(e, states, vstride, lane_boff, f); break;
         case 3: entry_batch<3, ST>(e, states, vstride, lane_boff, f); break;
-        case 4: entry_batch<4, ST>(e, states, vstride, lane_boff, f); break;
-        case 5: entry_batch<5, ST>(e, states, vstride, lane_boff, f); break;
-        case 6: entry_batch<6, ST>(e, states, vstride, lane_boff, f); break;
-        case 7: entry_batch<7, ST>(e, states, vstride, lane_boff, f); break;
-        default: entry_batch<8, ST>(e, states, vstride, lane_boff, f); break;
+        default: entry_batch<kEntryBatch, ST>(e, states, vstride, lane_boff, f); break;
         }
     }
 }
@@ -469,7 +465,8 @@ struct Work {
 constexpr uint32_t kXcds = 8;
 constexpr int kSweepQuadsPerLane = 1;  // column quads per lane in one sweep block
 constexpr int kMinSweepBlocks = 4096;  // replicas are split below this many blocks
-constexpr int64_t kMinSweepQuads = 64;  // narrowest column chunk of a fast sweep block (quads)
+constexpr int64_t kMinSweepQuads = 64;  // narrowest column chunk of a sweep block (quads)
+constexpr int64_t kMinGenQuads = 16;    // the same for the generic kernel's one-wave blocks
 constexpr int kCountQuadsPerLane = 8;  // adjacent columns (state quads) per lane and iteration of a count block
 
 __device__ __forceinline__ void decode_block(uint32_t b, uint32_t count, uint32_t &local,
@@ -703,6 +700,53 @@ __device__ __forceinline__ void item_product_flat(cint32_t *f, lds_char *lds, gl
     }
 }
 
+// ------------------------------------------------- latent columns of a block
+//
+// A sweep block lists the latent columns of its chunk in LDS before drawing:
+// lane l reads the obs word of columns c0 + 4l .. c0 + 4l + 3, and a
+// block-wide prefix sum (wave ballots, then the waves' totals) places them.
+struct LatentLanes {
+    int lat;  // the lane's latent mask
+    int pre;  // latent columns of the wave's lower lanes
+};
+
+// The lane's part; the waves' totals go to wave_n (LDS).  The caller
+// synchronises before latent_list.
+template <int BLOCK>
+__device__ __forceinline__ void latent_count(const SweepParams &P, const Work &W, LatentLanes &L,
+                                             int32_t *wave_n) {
+    const int64_t col = 4 * (W.q0 + (int64_t)threadIdx.x);
+    L.lat = col < W.q1 * 4 ? latent_bits(P, W.node, col) : 0;
+    const int cnt = __builtin_popcount(L.lat);
+    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
+    auto below = [](uint64_t b) {  // set lanes below this one
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+    };
+    L.pre = below(b0) + 2 * below(b1) + 4 * below(b2);
+    if ((threadIdx.x & 63) == 0)
+        wave_n[threadIdx.x >> 6] =
+            __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1) + 4 * __builtin_popcountll(b2);
+}
+
+// Lists the columns as offsets from c0 (ascending) and returns their number;
+// the caller synchronises before reading the list.
+template <int BLOCK>
+__device__ __forceinline__ int latent_list(const LatentLanes &L, const int32_t *wave_n, uint16_t *lcol) {
+    const int wave = threadIdx.x >> 6;
+    int base = 0, ncl = 0;
+#pragma unroll
+    for (int v = 0; v < BLOCK / 64; ++v) {
+        const int nv = wave_n[v];
+        base += v < wave ? nv : 0;
+        ncl += nv;
+    }
+    int pos = base + L.pre;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if ((L.lat >> c) & 1) lcol[pos++] = (uint16_t)(4 * threadIdx.x + c);
+    return ncl;
+}
+
 // The block's latent columns and its replica range, as items.
 struct Items {
     const uint16_t *col;  // latent columns of the chunk, as offsets from c0 (LDS)
@@ -710,6 +754,18 @@ struct Items {
     int ncl, nrq, r0, r1;
     float inv;            // 1 / ncl
 };
+
+__device__ __forceinline__ Items block_items(const Work &W, const uint16_t *lcol, int ncl) {
+    Items I;
+    I.col = lcol;
+    I.c0 = W.q0 * 4;
+    I.ncl = ncl;
+    I.r0 = W.r0;
+    I.r1 = W.r1;
+    I.nrq = (W.r1 - W.r0 + 3) >> 2;
+    I.inv = 1.f / (float)ncl;
+    return I;
+}
 
 // Item t -> (column j, first replica rb, replicas nrep).
 __device__ __forceinline__ void item_of(const Items &I, int t, int64_t &j, int &rb, int &nrep) {
@@ -930,20 +986,8 @@ __global__ __launch_bounds__(kSweepBlock, DEBUG ? 1 : kSweepWaves) void sweep_fa
     const int mode = d[2];
     const float *tab = P.table + d[3];
     const uint32_t *cond = P.cond + d[5];
-    // latent columns of the chunk: lane l reads the obs word of columns
-    // c0 + 4l .. c0 + 4l + 3
-    const int64_t c0 = W.q0 * 4;
-    const int64_t col = c0 + 4 * (int64_t)threadIdx.x;
-    const int lat = col < W.q1 * 4 ? latent_bits(P, W.node, col) : 0;
-    const int cnt = __builtin_popcount(lat);
-    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
-    auto below = [](uint64_t b) {  // set lanes below this one
-        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-    };
-    const int pre = below(b0) + 2 * below(b1) + 4 * below(b2);
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
-        wave_n[wave] = __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1) + 4 * __builtin_popcountll(b2);
+    LatentLanes L;
+    latent_count<kSweepBlock>(P, W, L, wave_n);
     if (STAGED) {
         const float4 *src = reinterpret_cast<const float4 *>(mode == kModeTable ? (const void *)cond
                                                                                 : (const void *)tab);
@@ -951,27 +995,10 @@ __global__ __launch_bounds__(kSweepBlock, DEBUG ? 1 : kSweepWaves) void sweep_fa
         for (int i = threadIdx.x; i < len4; i += kSweepBlock) lds4[i] = src[i];
     }
     __syncthreads();
-    int base = 0, ncl = 0;
-#pragma unroll
-    for (int v = 0; v < kSweepBlock / 64; ++v) {
-        const int nv = wave_n[v];
-        base += v < wave ? nv : 0;
-        ncl += nv;
-    }
-    int pos = base + pre;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        if ((lat >> c) & 1) lcol[pos++] = (uint16_t)(4 * threadIdx.x + c);
+    const int ncl = latent_list<kSweepBlock>(L, wave_n, lcol);
     __syncthreads();
     if (ncl == 0) return;  // uniform
-    Items I;
-    I.col = lcol;
-    I.c0 = c0;
-    I.ncl = ncl;
-    I.r0 = W.r0;
-    I.r1 = W.r1;
-    I.nrq = (W.r1 - W.r0 + 3) >> 2;
-    I.inv = 1.f / (float)ncl;
+    const Items I = block_items(W, lcol, ncl);
     lds_char *lds = (lds_char *)lds4;
     global_char *gt = scalar_global_ptr(tab);
     if (mode == kModeKP2) sweep_product<2, ST, DEBUG, STAGED>(P, W, I, lds, gt);
@@ -989,9 +1016,12 @@ __global__ __launch_bounds__(kSweepBlock, DEBUG ? 1 : kSweepWaves) void sweep_fa
 }
 
 // Wide path (class 2): product modes with KP up to 16 and any record size,
-// 32-bit float offsets, tables in global memory.
+// 32-bit float offsets, tables in global memory.  The block's items (latent
+// column, replica quad) one per lane at a time, as in the fast kernel: lanes
+// of observed columns would wait out the conditionals of the others (70% of
+// them at 30% missing).
 template <int KP, typename ST, bool DEBUG>
-__device__ void sweep_wide(const SweepParams &P, const Work &W) {
+__device__ void sweep_wide(const SweepParams &P, const Work &W, const Items &I) {
     using Q = Quad<ST>;
     cint32_t *d = W.d;
     const int K = d[0], n_groups = d[10];
@@ -1000,17 +1030,11 @@ __device__ void sweep_wide(const SweepParams &P, const Work &W) {
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
-    // lanes take (column, replica quad) pairs, consecutive lanes consecutive
-    // columns of one quad
-    const int64_t c0 = W.q0 * 4;
-    const int ncols = (int)((W.q1 * 4 < P.n_cols ? W.q1 * 4 : P.n_cols) - c0);
-    const int nrq = (W.r1 - W.r0 + 3) >> 2;
-    for (int t = threadIdx.x; t < ncols * nrq; t += kSweepBlock) {
-        const int rq = t / ncols;
-        const int64_t j = c0 + (t - rq * ncols);
-        if (P.obs[(int64_t)W.node * P.ld + j] != 0) continue;
-        const int rb = W.r0 + 4 * rq;
-        const int nrep = W.r1 - rb < 4 ? W.r1 - rb : 4;
+    const int n_items = I.ncl * I.nrq;
+    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
+        int64_t j;
+        int rb, nrep;
+        item_of(I, t, j, rb, nrep);
         const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
         typename Q::V cur = load_row<ST>(states, W.node, vstride, qoff);
         float w[4][KP];
@@ -1044,99 +1068,231 @@ __device__ void sweep_wide(const SweepParams &P, const Work &W) {
 template <typename ST, bool DEBUG>
 __global__ __launch_bounds__(kSweepBlock) void sweep_wide_kernel(SweepParams P) {
     if (P.ids) P.sweep_id = P.ids[0];
+    __shared__ uint16_t lcol[4 * kSweepBlock];
+    __shared__ int32_t wave_n[kSweepBlock / 64];
     const Work W = block_work(P);
+    if (W.q0 >= W.q1) return;  // uniform across the block
+    LatentLanes L;
+    latent_count<kSweepBlock>(P, W, L, wave_n);
+    __syncthreads();
+    const int ncl = latent_list<kSweepBlock>(L, wave_n, lcol);
+    __syncthreads();
+    if (ncl == 0) return;  // uniform
+    const Items I = block_items(W, lcol, ncl);
     const int KP = W.d[1];
-    if (KP == 2) sweep_wide<2, ST, DEBUG>(P, W);
-    else if (KP == 4) sweep_wide<4, ST, DEBUG>(P, W);
-    else if (KP == 6) sweep_wide<6, ST, DEBUG>(P, W);
-    else if (KP == 8) sweep_wide<8, ST, DEBUG>(P, W);
-    else sweep_wide<16, ST, DEBUG>(P, W);
+    if (KP == 2) sweep_wide<2, ST, DEBUG>(P, W, I);
+    else if (KP == 4) sweep_wide<4, ST, DEBUG>(P, W, I);
+    else if (KP == 6) sweep_wide<6, ST, DEBUG>(P, W, I);
+    else if (KP == 8) sweep_wide<8, ST, DEBUG>(P, W, I);
+    else sweep_wide<16, ST, DEBUG>(P, W, I);
 }
 
 // ------------------------------------------------- generic path, K_i > 16
 //
 // The weight of state k is kept as (mantissa in [0.5, 1), exponent) and
-// renormalised exactly after every factor, so any K fits in a few registers;
-// the three passes (largest exponent, total, search) each recompute the
-// products by walking the node's wide list for one column.
+// renormalised exactly after every factor, so any K and any number of
+// factors fit.  A block is one wave.  Its items are (latent column, replica):
+// 64 of them at a time, one per lane, have their k-vectors' offsets formed
+// from the blanket's states (offsets in LDS); then a team of 16 lanes takes
+// an item's k-vectors, four states per lane, so that each factor is one
+// 256-byte read of consecutive floats, and leaves the scaled weights in LDS;
+// then each lane sums and searches its own item's weights in ascending k.
+// The blanket is walked once per draw, and a launch has enough waves for the
+// device.  Bound by the latency of those reads and, per state, four exact
+// renormalising operations per factor.  A lane per (column, quad) that walked
+// the blanket again for every state and pass took 12.0 ms of a 12.3 ms step
+// of a 120-node network with ten such nodes (20,000 columns, m = 4); the
+// step now takes 0.49 ms.
+constexpr int kGenBlock = 64;     // one wave
+constexpr int kGenTeam = 16;      // lanes per item
+constexpr int kGenChunk = 4 * kGenTeam;   // states of a chunk: one float4 per lane of a team
+constexpr int kGenRow = kGenChunk + 4;    // LDS row of an item: 16 float4s and one of padding, so that
+                                          // 16 lanes reading their own rows' float4s hit 16 bank groups
+constexpr int kGenGroups = 16;    // k-vector offsets kept in LDS per item
+constexpr int kGenRounds = 4;     // items of a team whose reads are in flight together
+constexpr int kNoExp = -100000;   // below any exponent
 
+struct GenShared {
+    float w[kGenBlock * kGenRow];                // scaled weights of a chunk, by item
+    uint32_t idx[kGenGroups * kGenBlock];        // k-vector offsets, by group and item
+    int32_t top[kGenBlock];                      // largest exponent, by item
+};
+
+// The offsets of groups [g0, g0 + ng) of the lane's item; g: the wide list at
+// group g0, advanced past them.  (state element: slot r & 3 of quad r >> 2)
 template <typename ST>
-__device__ float weight_ext(cint32_t *d, const float *__restrict__ tab, const char *__restrict__ base,
-                            int64_t vstride, int c, int k, int &e) {
+__device__ __forceinline__ void gen_offsets(cint32_t *&g, int ng, const void *states, int64_t vstride,
+                                            uint32_t qoff, int slot, uint32_t *idx) {
     using Q = Quad<ST>;
-    cint32_t *g = d + d[11];
-    const int n_groups = d[10];
-    float mnt = 1.f;
-    e = 0;
-    for (int j = 0; j < n_groups; ++j) {
+    for (int j = 0; j < ng; ++j) {
+        uint32_t at = (uint32_t)g[1];
         const int n_e = g[0];
-        uint32_t idx = (uint32_t)g[1];
-        for (int t = 0; t < n_e; ++t)
-            idx += (uint32_t)Q::get(Q::load_at(base + (int64_t)g[2 + 2 * t] * vstride), c) *
-                   (uint32_t)g[3 + 2 * t];
+        auto acc = [&](typename Q::V v, uint32_t mult) { at += (uint32_t)Q::get(v, slot) * mult; };
+        walk_entries<ST>(g + 2, n_e, states, vstride, qoff, acc);
         g += 2 + 2 * n_e;
-        mnt *= tab[idx + k];
-        const int de = __builtin_amdgcn_frexp_expf(mnt);
-        mnt = __builtin_ldexpf(mnt, -de);
-        e += de;
+        idx[j * kGenBlock + threadIdx.x] = at;
     }
-    return mnt;
+}
+
+// Multiplies the k-vectors of ng groups into the weights of states k .. k + 3
+// of items it[0 .. R).
+template <int R>
+__device__ __forceinline__ void gen_multiply(const GenShared &S, const float *__restrict__ tab, int ng, int k,
+                                             const int (&it)[R], float (&w)[R][4], int (&e)[R][4]) {
+    for (int j = 0; j < ng; ++j) {
+        float4 f[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            f[r] = *reinterpret_cast<const float4 *>(tab + S.idx[j * kGenBlock + it[r]] + k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float x[4] = {f[r].x, f[r].y, f[r].z, f[r].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float p = w[r][c] * x[c];
+                const int de = __builtin_amdgcn_frexp_expf(p);
+                w[r][c] = __builtin_ldexpf(p, -de);
+                e[r][c] += de;
+            }
+        }
+    }
 }
 
 template <typename ST, bool DEBUG>
-__global__ __launch_bounds__(kSweepBlock) void sweep_generic_kernel(SweepParams P) {
+__global__ __launch_bounds__(kGenBlock) void sweep_generic_kernel(SweepParams P) {
     if (P.ids) P.sweep_id = P.ids[0];
     using Q = Quad<ST>;
+    using E = typename ElemOf<ST>::T;
+    __shared__ uint16_t lcol[4 * kGenBlock];
+    __shared__ int32_t wave_n[1];
+    __shared__ __align__(16) GenShared S;
     const Work W = block_work(P);
+    if (W.q0 >= W.q1) return;  // uniform across the block
+    LatentLanes L;
+    latent_count<kGenBlock>(P, W, L, wave_n);
+    __syncthreads();
+    const int ncl = latent_list<kGenBlock>(L, wave_n, lcol);
+    __syncthreads();
+    if (ncl == 0) return;  // uniform
     cint32_t *d = W.d;
-    const int K = d[0];
+    const int K = d[0], KP = d[1], n_groups = d[10];
     const float *tab = P.table + d[3];
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
-    const int64_t c0 = W.q0 * 4;
-    const int ncols = (int)((W.q1 * 4 < P.n_cols ? W.q1 * 4 : P.n_cols) - c0);
-    const int nrq = (W.r1 - W.r0 + 3) >> 2;
-    for (int t = threadIdx.x; t < ncols * nrq; t += kSweepBlock) {
-        const int rq = t / ncols;
-        const int64_t j = c0 + (t - rq * ncols);
-        if (P.obs[(int64_t)W.node * P.ld + j] != 0) continue;
-        const int rb = W.r0 + 4 * rq;
-        const int nrep = W.r1 - rb < 4 ? W.r1 - rb : 4;
-        const int64_t qe = quad_boff<ST>(rb >> 2, P.ld, j);  // the quad's byte offset in a node block
-        const char *base = states + qe;
-        char *own = states + (int64_t)W.node * vstride + qe;
-        typename Q::V cur = Q::load_at(own);
-        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
-        for (int c = 0; c < nrep; ++c) {
-            int E = -100000;
-            for (int k = 0; k < K; ++k) {
-                int e;
-                const float mk = weight_ext<ST>(d, tab, base, vstride, c, k, e);
-                if (mk > 0.f && e > E) E = e;
+    const int lane = threadIdx.x, team = lane / kGenTeam, tl = lane % kGenTeam;
+    const int n_items = ncl * (W.r1 - W.r0);
+    for (int t0 = 0; t0 < n_items; t0 += kGenBlock) {
+        // the lane's item (a spare lane of the last batch repeats item t0)
+        const int n_it = n_items - t0 < kGenBlock ? n_items - t0 : kGenBlock;
+        const int t = lane < n_it ? t0 + lane : t0;
+        const int r = W.r0 + t / ncl;
+        const int64_t j = W.q0 * 4 + lcol[t % ncl];
+        const uint32_t qoff = quad_boff<ST>(r >> 2, P.ld, j);
+        cint32_t *g = d + d[11];
+        const int ng0 = n_groups < kGenGroups ? n_groups : kGenGroups;
+        gen_offsets<ST>(g, ng0, states, vstride, qoff, r & 3, S.idx);
+        S.top[lane] = kNoExp;
+        __syncthreads();
+        // Passes over the chunks of states: 0 finds each item's largest
+        // exponent, 1 leaves the scaled weights and totals them, 2 leaves them
+        // again and searches.  With one chunk (K <= kGenChunk) one run over it
+        // leaves the weights for both the total and the search.
+        const bool single = K <= kGenChunk;
+        float Z = 0.f, Sk = 0.f, t_u = 0.f;
+        int pick = -1, last_pos = 0;
+        for (int pass = single ? 1 : 0; pass < 3; ++pass) {
+            if (pass == 2) {
+                const Philox4 rnd = gibbs_block(P, W.node, r >> 2, j);
+                const uint32_t word = (r & 3) == 0 ? rnd.w[0] : (r & 3) == 1 ? rnd.w[1]
+                                    : (r & 3) == 2 ? rnd.w[2] : rnd.w[3];
+                t_u = uniform24(word) * Z;
             }
-            float Z = 0.f;
-            for (int k = 0; k < K; ++k) {
-                int e;
-                const float mk = weight_ext<ST>(d, tab, base, vstride, c, k, e);
-                Z += __builtin_ldexpf(mk, e - E);
+            for (int k0 = 0; k0 < K; k0 += kGenChunk) {
+                const int k = k0 + 4 * tl;
+                // pass 2 of a single chunk finds its weights in place
+                for (int i0 = 0; i0 < n_it && !(single && pass == 2); i0 += kGenRounds * (kGenBlock / kGenTeam)) {
+                    int it[kGenRounds], e[kGenRounds][4];
+                    float w[kGenRounds][4];
+#pragma unroll
+                    for (int q = 0; q < kGenRounds; ++q) {
+                        it[q] = i0 + q * (kGenBlock / kGenTeam) + team;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            w[q][c] = k + c < K ? 1.f : 0.f;
+                            e[q][c] = 0;
+                        }
+                    }
+                    if (k < KP) gen_multiply<kGenRounds>(S, tab, ng0, k, it, w, e);
+                    // nodes with more groups than LDS keeps offsets of: the
+                    // rest in runs, each formed by all lanes for their items
+                    cint32_t *gr = g;
+                    for (int gb = ng0; gb < n_groups; gb += kGenGroups) {
+                        const int ng = n_groups - gb < kGenGroups ? n_groups - gb : kGenGroups;
+                        __syncthreads();
+                        gen_offsets<ST>(gr, ng, states, vstride, qoff, r & 3, S.idx);
+                        __syncthreads();
+                        if (k < KP) gen_multiply<kGenRounds>(S, tab, ng, k, it, w, e);
+                    }
+                    if (ng0 < n_groups) {  // the first run again, for the next items
+                        cint32_t *gf = d + d[11];
+                        __syncthreads();
+                        gen_offsets<ST>(gf, ng0, states, vstride, qoff, r & 3, S.idx);
+                        __syncthreads();
+                    }
+#pragma unroll
+                    for (int q = 0; q < kGenRounds; ++q) {
+                        int top = kNoExp;
+                        if (pass == 0 || single) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                if (w[q][c] > 0.f && e[q][c] > top) top = e[q][c];
+#pragma unroll
+                            for (int s = kGenTeam / 2; s > 0; s >>= 1) {
+                                const int o = __shfl_xor(top, s);
+                                top = o > top ? o : top;
+                            }
+                        }
+                        if (pass == 0) {
+                            if (tl == 0 && top > S.top[it[q]]) S.top[it[q]] = top;
+                        } else {
+                            if (!single) top = S.top[it[q]];
+                            float4 v;
+                            v.x = __builtin_ldexpf(w[q][0], e[q][0] - top);
+                            v.y = __builtin_ldexpf(w[q][1], e[q][1] - top);
+                            v.z = __builtin_ldexpf(w[q][2], e[q][2] - top);
+                            v.w = __builtin_ldexpf(w[q][3], e[q][3] - top);
+                            *reinterpret_cast<float4 *>(S.w + it[q] * kGenRow + 4 * tl) = v;
+                        }
+                    }
+                }
+                __syncthreads();
+                if (pass == 0) continue;
+                const int kn = K - k0 < kGenChunk ? K - k0 : kGenChunk;
+                for (int q = 0; 4 * q < kn; ++q) {
+                    const float4 v = *reinterpret_cast<const float4 *>(S.w + lane * kGenRow + 4 * q);
+                    const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int kk = k0 + 4 * q + c;
+                        if (pass == 1) {
+                            Z += x[c];  // states past K hold 0
+                        } else {
+                            Sk += x[c];
+                            if (x[c] > 0.f) last_pos = kk;
+                            if (pick < 0 && t_u < Sk && kk < K) pick = kk;
+                            if (DEBUG && lane < n_it && kk < K && j >= P.win_begin && j < P.win_begin + P.win)
+                                P.probs[(((int64_t)W.node * P.m + r) * P.win + (j - P.win_begin)) * P.max_card + kk] =
+                                    x[c] / Z;
+                        }
+                    }
+                }
+                __syncthreads();
             }
-            const float t_u = uniform24(rnd.w[c]) * Z;
-            float S = 0.f;
-            int pick = -1, last_pos = 0;
-            for (int k = 0; k < K; ++k) {
-                int e;
-                const float wk = __builtin_ldexpf(weight_ext<ST>(d, tab, base, vstride, c, k, e), e - E);
-                S += wk;
-                if (wk > 0.f) last_pos = k;
-                if (pick < 0 && t_u < S) pick = k;
-                if (DEBUG && j >= P.win_begin && j < P.win_begin + P.win)
-                    P.probs[(((int64_t)W.node * P.m + rb + c) * P.win + (j - P.win_begin)) * P.max_card + k] =
-                        wk / Z;
-            }
-            if (pick < 0) pick = last_pos;
-            cur = Q::put(cur, c, pick);
         }
-        Q::store_at(own, cur);
+        if (pick < 0) pick = last_pos;
+        // the item's own slot: other lanes write the quad's other slots
+        if (lane < n_it)
+            reinterpret_cast<E *>(states + (int64_t)W.node * vstride + qoff)[r & 3] = (E)pick;
     }
 }
 
@@ -2083,8 +2239,12 @@ void sweep_class(const SweepParams &P, int32_t klass, int32_t lds_bytes, dim3 gr
         if (dbg) hipLaunchKernelGGL((dev::sweep_wide_kernel<ST, true>), grid, blk, 0, stream, P);
         else hipLaunchKernelGGL((dev::sweep_wide_kernel<ST, false>), grid, blk, 0, stream, P);
     } else {
-        if (dbg) hipLaunchKernelGGL((dev::sweep_generic_kernel<ST, true>), grid, blk, 0, stream, P);
-        else hipLaunchKernelGGL((dev::sweep_generic_kernel<ST, false>), grid, blk, 0, stream, P);
+        // K > 16 is never stored in 4 bits
+        if constexpr (!std::is_same<ST, dev::Nib>::value) {
+            const dim3 gb(dev::kGenBlock);
+            if (dbg) hipLaunchKernelGGL((dev::sweep_generic_kernel<ST, true>), grid, gb, 0, stream, P);
+            else hipLaunchKernelGGL((dev::sweep_generic_kernel<ST, false>), grid, gb, 0, stream, P);
+        }
     }
 }
 
@@ -2102,17 +2262,19 @@ hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t kla
     // faster).  A block's replica range is always whole state quads (the
     // last one ends at m), so that no two blocks write one quad.
     const int64_t quads = (P.n_cols + 3) / 4;
-    P.quads_per_block = (int64_t)dev::kSweepBlock * dev::kSweepQuadsPerLane;
+    P.quads_per_block = klass == 3 ? (int64_t)dev::kGenBlock
+                                   : (int64_t)dev::kSweepBlock * dev::kSweepQuadsPerLane;
     // the fast kernel draws replicas in quads (one Philox block each), so a
     // block's replica range is whole quads except at the end
     const int64_t m_quads = (P.m + 3) / 4;
     // small launches (few nodes or columns) take narrower column chunks, down
-    // to 256 columns, so that even with one replica quad per block they fill
-    // the device with blocks
-    if (klass <= 1)
-        while (P.quads_per_block > dev::kMinSweepQuads &&
-               count * ((quads + P.quads_per_block - 1) / P.quads_per_block) * m_quads < dev::kMinSweepBlocks)
-            P.quads_per_block /= 2;
+    // to 256 columns (64 for the one-wave blocks of the generic kernel), so
+    // that even with one replica quad per block they fill the device with
+    // blocks
+    const int64_t min_quads = klass == 3 ? dev::kMinGenQuads : dev::kMinSweepQuads;
+    while (P.quads_per_block > min_quads &&
+           count * ((quads + P.quads_per_block - 1) / P.quads_per_block) * m_quads < dev::kMinSweepBlocks)
+        P.quads_per_block /= 2;
     const int64_t chunks = (quads + P.quads_per_block - 1) / P.quads_per_block;
     int64_t rsplit = klass == 0 ? (dev::kMinSweepBlocks + count * chunks - 1) / (count * chunks) : m_quads;
     if (rsplit > m_quads) rsplit = m_quads;

@@ -266,6 +266,36 @@ def test_int16_states(table_limit, variant):
     _custom_case(net, st, ob, th, 2, 300, win=(0, 64), table_limit=table_limit, **variant)
 
 
+@pytest.mark.parametrize("K,n_kids,n_cols,m", [
+    (17, 2, 1, 1),        # one item
+    (17, 20, 257, 3),     # more child groups than the kernel keeps offsets of, a second column chunk
+    (63, 2, 130, 5),      # a last float4 with one padded state, two replica quads
+    (64, 3, 200, 4),      # exactly one chunk of states
+    (65, 17, 90, 4),      # a second chunk of one state, more groups than offsets
+    (129, 2, 70, 2),      # three chunks
+])
+@pytest.mark.parametrize("wide", [False, True], ids=["int8", "int16"])
+def test_generic_kernel_edges(K, n_kids, n_cols, m, wide):
+    """Nodes of more than 16 states: one item, the 64-state chunk boundary,
+    the 16 groups whose offsets are kept, partial batches of 64 items."""
+    parents = [[], [0]] + [[0, 1] if k % 3 == 0 else [0] for k in range(n_kids)]
+    card = [K, 3] + [2 + k % 3 for k in range(n_kids)]
+    if wide:
+        parents, card = parents + [[]], card + [130]
+    net, st, ob, th = _custom(parents, card, n_cols, m, 0.6, 100 + K)
+    _custom_case(net, st, ob, th, m, n_cols, win=(0, min(n_cols, 64)))
+
+
+@pytest.mark.parametrize("K,n_cols,m", [(9, 1, 1), (10, 1027, 5), (16, 300, 8)])
+@pytest.mark.parametrize("bits", [0, 4])
+def test_wide_kernel_edges(K, n_cols, m, bits):
+    """The 32-bit index kernel lists its latent columns: one item, a second
+    column chunk with a partial replica quad, whole quads."""
+    net, st, ob, th = _custom([[], [0], [0, 1], [1]], [K, 3, K, 2], n_cols, m, 0.4, 60 + K)
+    kw = dict(state_bits=bits) if bits else {}
+    _custom_case(net, st, ob, th, m, n_cols, win=(0, min(n_cols, 64)), table_limit=0, **kw)
+
+
 def test_large_replica_count_and_column_offset():
     net, st, ob, th = _custom([[], [0], [0, 1], [2], [3, 1]], [2, 3, 2, 4, 2], 256, 37, 0.5, 4)
     _custom_case(net, st, ob, th, 37, 256, col_offset=(1 << 32) - 8192, win=(0, 32))
