@@ -99,7 +99,7 @@ void free_tables(same::DeviceTables &t) {
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(t.device);
     void *ptrs[] = {t.desc, t.desc_off, t.order, t.cdesc, t.cdesc_off, t.cwork, t.segs, t.blk_seg,
-                    t.blk_first, t.row_off, t.row_k, t.cprog, t.cprog_off, t.cblk_prog, t.cblk_first};
+                    t.blk_first, t.row_off, t.row_k, t.tile_row, t.long_row, t.cprog, t.cprog_off, t.cblk_prog, t.cblk_first};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (cur >= 0) (void)hipSetDevice(cur);
@@ -151,6 +151,10 @@ int tables_for_current_device(same_ctx *ctx, same::DeviceTables **out) {
     if (r == hipSuccess) r = upload(&nt.blk_first, blk_first);
     if (r == hipSuccess) r = upload(&nt.row_off, g.row_off);
     if (r == hipSuccess) r = upload(&nt.row_k, g.row_k);
+    if (r == hipSuccess) r = upload(&nt.tile_row, g.tile_row);
+    if (r == hipSuccess) r = upload(&nt.long_row, g.long_row);
+    nt.n_tiles = (int32_t)(g.tile_row.size() / 2);
+    nt.n_long = (int32_t)g.long_row.size();
     if (r == hipSuccess) r = upload(&nt.cprog, g.cprog);
     if (r == hipSuccess) r = upload(&nt.cprog_off, g.cprog_off);
     if (r == hipSuccess) r = upload(&nt.cblk_prog, cblk_prog);
@@ -418,6 +422,12 @@ int do_sweep(same_ctx *ctx, void *states, const uint8_t *obs, const float *cpts,
     return SAME_OK;
 }
 
+same::GammaArgs gamma_args(const same_ctx *ctx, uint64_t seed, uint32_t update_id, const uint32_t *ids,
+                           void *workspace) {
+    return same::GammaArgs{ctx->alpha, (uint32_t)seed, (uint32_t)(seed >> 32), update_id, ids,
+                           (double *)((char *)workspace + ctx->ws_gamma)};
+}
+
 // Sweep, counts with the moving sum, and the Dirichlet resample of one
 // minibatch, tile by tile for the sweep and counts.
 // ids (nullable, device): the sweep and update ids are read there at launch
@@ -451,14 +461,10 @@ int do_step(same_ctx *ctx, void *states, const uint8_t *obs, float *cpts, int32_
                        "count launch");
         if (rc) return rc;
     }
-    // the moving sum and the Dirichlet resample (same_sample_cpts), with the
-    // moving sum fused into the Gamma launch
-    double *gv = (double *)((char *)workspace + ctx->ws_gamma);
-    rc = check_hip(same::launch_moving_sum_gamma(newc, mb_counts, totals, ctx->alpha, (uint32_t)seed,
-                                                 (uint32_t)(seed >> 32), update_id, ids, gv, total, s),
-                   "moving-sum and gamma launch");
-    if (rc) return rc;
-    return check_hip(same::launch_normalize(*t, gv, cpts, ctx->g.n_rows, s), "normalize launch");
+    // the moving sum and the Dirichlet resample (same_sample_cpts) in one launch
+    return check_hip(same::launch_moving_resample(*t, newc, mb_counts, totals,
+                                                  gamma_args(ctx, seed, update_id, ids, workspace), cpts, s),
+                     "moving-sum and resample launch");
 }
 
 // Device slot geometry of the out-of-core passes.
@@ -654,13 +660,9 @@ int same_sample_cpts(same_ctx *ctx, const int32_t *totals, float *cpts_out, uint
     int rc = tables_for_current_device(ctx, &t);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const int64_t total = ctx->g.off[ctx->g.n];
-    double *gv = (double *)((char *)workspace + ctx->ws_gamma);
-    rc = check_hip(same::launch_gamma(totals, ctx->alpha, (uint32_t)seed, (uint32_t)(seed >> 32), update_id,
-                                      nullptr, gv, total, s),
-                   "gamma launch");
-    if (rc) return rc;
-    return check_hip(same::launch_normalize(*t, gv, cpts_out, ctx->g.n_rows, s), "normalize launch");
+    return check_hip(same::launch_resample(*t, totals, gamma_args(ctx, seed, update_id, nullptr, workspace),
+                                           cpts_out, s),
+                     "resample launch");
 }
 
 int same_sweep_plan(const same_ctx *ctx, int32_t m, int64_t n_cols, int64_t *tile_cols_out,
@@ -868,13 +870,9 @@ int same_sample_cpts_ema(same_ctx *ctx, const double *totals, float *cpts_out, u
     int rc = tables_for_current_device(ctx, &t);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    const int64_t total = ctx->g.off[ctx->g.n];
-    double *gv = (double *)((char *)workspace + ctx->ws_gamma);
-    rc = check_hip(same::launch_gamma(totals, ctx->alpha, (uint32_t)seed, (uint32_t)(seed >> 32), update_id,
-                                      nullptr, gv, total, s),
-                   "gamma launch");
-    if (rc) return rc;
-    return check_hip(same::launch_normalize(*t, gv, cpts_out, ctx->g.n_rows, s), "normalize launch");
+    return check_hip(same::launch_resample(*t, totals, gamma_args(ctx, seed, update_id, nullptr, workspace),
+                                           cpts_out, s),
+                     "resample launch");
 }
 
 int same_stream_pass_ema(same_ctx *ctx, void *host_states, const uint8_t *host_obs, int64_t host_ld,

@@ -615,6 +615,21 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
             g.row_off.push_back((int32_t)(g.off[i] + u * card[i]));
             g.row_k.push_back(card[i]);
         }
+    int32_t filled = kResampleTile;  // entries of the open tile
+    for (size_t r = 0; r < g.row_k.size(); ++r) {
+        if (g.row_k[r] > kResampleTile) {
+            g.long_row.push_back((int32_t)r);
+            filled = kResampleTile;
+            continue;
+        }
+        if (filled + g.row_k[r] > kResampleTile) {
+            g.tile_row.push_back((int32_t)r);
+            g.tile_row.push_back(0);
+            filled = 0;
+        }
+        filled += g.row_k[r];
+        g.tile_row.back() += 1;
+    }
     return SAME_OK;
 }
 

@@ -72,6 +72,7 @@ constexpr int64_t kDefaultTableLimit = kDefaultLdsBytes / 4;
 constexpr int32_t kDescHeader = 16;
 constexpr int64_t kPackedLimit = 65536;      // packed indices are 16-bit
 constexpr int32_t kCountLdsBins = 8192;      // bins of the count kernel's LDS histogram
+constexpr int32_t kResampleTile = 256;       // CPT entries of a resample block
 constexpr int64_t kCountSplitBins = 4 * kCountLdsBins;  // largest CPT counted in ranges
 
 // Sweep descriptor of a node (int32 words at desc_off[i]):
@@ -170,6 +171,9 @@ struct Compiled {
 
     // CPT rows, for the Dirichlet normalisation: entry offset and K of each row
     std::vector<int32_t> row_off, row_k;
+    // resample tiles (first row, rows) of at most kResampleTile entries, and
+    // the rows longer than that
+    std::vector<int32_t> tile_row, long_row;
 };
 
 // Returns 0 or a negative SAME_E* code with a message in err.

@@ -1741,56 +1741,179 @@ __global__ void moving_sum_kernel(const int32_t *__restrict__ newc, int32_t *__r
 // Gamma(a) = Gamma(a + 1) * U^(1/a).  Attempt t uses the Philox block at
 // counter {e, t, 1 << 24, q}: Box-Muller normal from words 0 and 1, the
 // acceptance uniform from word 2 and the boost uniform from word 3.
-__device__ double gamma_mt(double a, uint32_t e, uint32_t q, uint32_t k0, uint32_t k1) {
+struct GammaTry {
+    double z, v, ua, ub;  // normal, 1 + c z, acceptance and boost uniforms
+};
+
+__device__ __forceinline__ GammaTry gamma_try(double c, uint32_t e, uint32_t t, uint32_t q, uint32_t k0,
+                                              uint32_t k1) {
 #pragma clang fp contract(off)
-    const bool boost = a < 1.0;
-    const double b = boost ? a + 1.0 : a;
-    const double d = b - 1.0 / 3.0;
+    const Philox4 w = philox4x32_10(e, t, 1u << 24, q, k0, k1);
+    const double u1 = ((double)(w.w[0] >> 8) + 1.0) * 0x1p-24;
+    const double u2 = (double)(w.w[1] >> 8) * 0x1p-24;
+    GammaTry y;
+    y.z = sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2);
+    y.v = 1.0 + c * y.z;
+    y.ua = ((double)(w.w[2] >> 8) + 1.0) * 0x1p-24;
+    y.ub = ((double)(w.w[3] >> 8) + 1.0) * 0x1p-24;
+    return y;
+}
+
+// Without the boost factor; ub: the boost uniform of the accepted attempt.
+__device__ __forceinline__ double gamma_mt(double a, uint32_t e, uint32_t q, uint32_t k0, uint32_t k1,
+                                           double &ub) {
+#pragma clang fp contract(off)
+    const double d = (a < 1.0 ? a + 1.0 : a) - 1.0 / 3.0;
     const double c = 1.0 / sqrt(9.0 * d);
+    ub = 1.0;
     for (uint32_t t = 0; t < 256; ++t) {
-        const Philox4 w = philox4x32_10(e, t, 1u << 24, q, k0, k1);
-        const double u1 = ((double)(w.w[0] >> 8) + 1.0) * 0x1p-24;
-        const double u2 = (double)(w.w[1] >> 8) * 0x1p-24;
-        const double z = sqrt(-2.0 * log(u1)) * cos(6.283185307179586476925286766559 * u2);
-        double v = 1.0 + c * z;
-        if (v <= 0.0) continue;
-        v = v * v * v;
-        const double ua = ((double)(w.w[2] >> 8) + 1.0) * 0x1p-24;
-        if (log(ua) < 0.5 * z * z + d - d * v + d * log(v)) {
-            double gv = d * v;
-            if (boost) gv *= pow(((double)(w.w[3] >> 8) + 1.0) * 0x1p-24, 1.0 / a);
-            return gv;
+        const GammaTry y = gamma_try(c, e, t, q, k0, k1);
+        if (y.v <= 0.0) continue;
+        const double v = y.v * y.v * y.v;
+        if (log(y.ua) < 0.5 * y.z * y.z + d - d * v + d * log(v)) {
+            ub = y.ub;
+            return d * v;
         }
     }
     return d;
 }
 
-template <typename T>
-__global__ void gamma_kernel(const T *__restrict__ totals, double alpha, uint32_t k0, uint32_t k1,
-                             uint32_t update_id, const uint32_t *__restrict__ ids, double *__restrict__ g,
-                             int64_t total) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const uint32_t u = ids ? ids[1] : update_id;
-    g[e] = gamma_mt(alpha + (double)totals[e], (uint32_t)e, u, k0, k1);
+// Dirichlet resample of one tile of whole CPT rows per block (at most
+// kResampleTile entries; longer rows have a kernel of their own): the moving sum of the
+// counts (MOVING), the Gamma draw of every entry, the row sums in ascending
+// order and the division, in one launch.
+//
+// Bound by the serial fp64 chain of the draws.  A lane's first attempt is
+// accepted where Marsaglia & Tsang's squeeze U < 1 - 0.0331 z^4 holds (it
+// implies the logarithmic test, with a margin of at least 9e-5 z^4 for every
+// shape >= 1: two logarithms saved for over nine draws in ten); the others --
+// whose retries every wave used to wait for, as 64 lanes rarely all accept at
+// once -- are listed and drawn from their first attempt on by as many lanes
+// as there are of them.  The rows are summed from LDS: one thread per row
+// that read its entries from memory took 55 us for rows of 130 states.
+// 815,059 entries in 196,000 rows: 27-32 us at 5 waves per SIMD (53 + 9 us as
+// a Gamma and a normalising launch); 26 entries 4.7 us (4.2 + 2.6 and a gap).
+constexpr int kResampleBlock = kResampleTile;
+
+// One piece of a resample: the shapes of the entries base .. base + n_e - 1
+// and their Gamma variates into gam.
+struct ResampleShared {
+    double gam[kResampleBlock], shape[kResampleBlock], sums[kResampleBlock];
+    uint16_t row_of_entry[kResampleBlock], list[kResampleBlock];
+    int32_t n_list;
+};
+
+template <typename T, bool MOVING>
+__device__ __forceinline__ void resample_draws(ResampleShared &S, int64_t base, int n_e,
+                                               const int32_t *__restrict__ newc, int32_t *__restrict__ mb,
+                                               T *__restrict__ totals, double alpha, uint32_t k0, uint32_t k1,
+                                               uint32_t u) {
+#pragma clang fp contract(off)
+    const int tid = (int)threadIdx.x;
+    const int64_t e = base + tid;
+    if (tid == 0) S.n_list = 0;
+    __syncthreads();
+    if (tid < n_e) {
+        double a;
+        if constexpr (MOVING) {
+            const int32_t nv = newc[e];
+            const int32_t delta = nv - mb[e];
+            mb[e] = nv;
+            const int32_t t = totals[e] + delta;
+            totals[e] = t;
+            a = alpha + (double)t;
+        } else {
+            a = alpha + (double)totals[e];
+        }
+        const double d = a - 1.0 / 3.0;
+        bool done = false;
+        if (!(a < 1.0)) {
+            const GammaTry y = gamma_try(1.0 / sqrt(9.0 * d), (uint32_t)e, 0u, u, k0, k1);
+            const double z2 = y.z * y.z;
+            done = y.v > 0.0 && y.ua < 1.0 - 0.0331 * (z2 * z2);
+            S.gam[tid] = d * (y.v * y.v * y.v);
+        }
+        if (!done) {
+            S.shape[tid] = a;
+            S.list[atomicAdd(&S.n_list, 1)] = (uint16_t)tid;
+        }
+    }
+    __syncthreads();
+    const int n_list = S.n_list;
+    for (int l = tid; l < n_list; l += kResampleBlock) {
+        const int x = S.list[l];
+        double ub;
+        S.gam[x] = gamma_mt(S.shape[x], (uint32_t)(base + x), u, k0, k1, ub);
+        S.sums[x] = ub;
+    }
+    if (alpha < 1.0) {  // the boost of shapes below one (all of them listed, each by this lane)
+        for (int l = tid; l < n_list; l += kResampleBlock) {
+            const int x = S.list[l];
+            const double a = S.shape[x];
+            if (a < 1.0) S.gam[x] *= pow(S.sums[x], 1.0 / a);
+        }
+    }
+    __syncthreads();
 }
 
-// The moving sum of a step's counts and the Gamma draw of every CPT entry
-// from the updated total, in one launch: per entry, the arithmetic of
-// moving_sum_kernel followed by that of gamma_kernel<int32_t>.
-__global__ void moving_sum_gamma_kernel(const int32_t *__restrict__ newc, int32_t *__restrict__ mb,
-                                        int32_t *__restrict__ totals, double alpha, uint32_t k0, uint32_t k1,
-                                        uint32_t update_id, const uint32_t *__restrict__ ids,
-                                        double *__restrict__ g, int64_t total) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const int32_t nv = newc[e];
-    const int32_t delta = nv - mb[e];
-    mb[e] = nv;
-    const int32_t t = totals[e] + delta;
-    totals[e] = t;
+template <typename T, bool MOVING>
+__global__ __launch_bounds__(kResampleBlock, 5) void resample_kernel(
+    const int32_t *__restrict__ tile_row, const int32_t *__restrict__ row_off, const int32_t *__restrict__ row_k,
+    const int32_t *__restrict__ newc, int32_t *__restrict__ mb, T *__restrict__ totals, double alpha, uint32_t k0,
+    uint32_t k1, uint32_t update_id, const uint32_t *__restrict__ ids, float *__restrict__ cpts) {
+#pragma clang fp contract(off)
+    __shared__ ResampleShared S;
+    const int tid = (int)threadIdx.x;
+    const int32_t r0 = as_const(tile_row)[2 * blockIdx.x], n_rows = as_const(tile_row)[2 * blockIdx.x + 1];
+    const int64_t first = as_const(row_off)[r0];
+    const int n_e = (int)(as_const(row_off)[r0 + n_rows - 1] - first) + as_const(row_k)[r0 + n_rows - 1];
     const uint32_t u = ids ? ids[1] : update_id;
-    g[e] = gamma_mt(alpha + (double)t, (uint32_t)e, u, k0, k1);
+    resample_draws<T, MOVING>(S, first, n_e, newc, mb, totals, alpha, k0, k1, u);
+    if (tid < n_rows) {
+        const int o = (int)(row_off[r0 + tid] - first), K = row_k[r0 + tid];
+        double s = 0.0;
+        for (int k = 0; k < K; ++k) {
+            s += S.gam[o + k];
+            S.row_of_entry[o + k] = (uint16_t)tid;
+        }
+        S.sums[tid] = s;
+    }
+    __syncthreads();
+    if (tid < n_e) {
+        const int r = S.row_of_entry[tid];
+        const double s = S.sums[r];
+        cpts[first + tid] = (float)(s > 0.0 ? S.gam[tid] / s : 1.0 / row_k[r0 + r]);
+    }
+}
+
+// A row longer than a tile, in pieces; its variates wait in g for its total.
+template <typename T, bool MOVING>
+__global__ __launch_bounds__(kResampleBlock) void resample_long_kernel(
+    const int32_t *__restrict__ long_row, const int32_t *__restrict__ row_off, const int32_t *__restrict__ row_k,
+    const int32_t *__restrict__ newc, int32_t *__restrict__ mb, T *__restrict__ totals, double alpha, uint32_t k0,
+    uint32_t k1, uint32_t update_id, const uint32_t *__restrict__ ids, double *__restrict__ g,
+    float *__restrict__ cpts) {
+#pragma clang fp contract(off)
+    __shared__ ResampleShared S;
+    const int tid = (int)threadIdx.x;
+    const int32_t r = as_const(long_row)[blockIdx.x];
+    const int64_t first = as_const(row_off)[r];
+    const int K = as_const(row_k)[r];
+    const uint32_t u = ids ? ids[1] : update_id;
+    double sum = 0.0;  // lane 0
+    for (int k0_ = 0; k0_ < K; k0_ += kResampleBlock) {
+        const int n_e = K - k0_ < kResampleBlock ? K - k0_ : kResampleBlock;
+        resample_draws<T, MOVING>(S, first + k0_, n_e, newc, mb, totals, alpha, k0, k1, u);
+        if (tid < n_e) g[first + k0_ + tid] = S.gam[tid];
+        if (tid == 0)
+            for (int k = 0; k < n_e; ++k) sum += S.gam[k];
+        __syncthreads();
+    }
+    if (tid == 0) S.sums[0] = sum;
+    __syncthreads();
+    const double s = S.sums[0];
+    for (int k = tid; k < K; k += kResampleBlock)  // each lane reads what it wrote
+        cpts[first + k] = (float)(s > 0.0 ? g[first + k] / s : 1.0 / K);
 }
 
 // The id pair of a replayed step graph moves on by (d0, d1) after the step.
@@ -1810,19 +1933,6 @@ __global__ void ema_kernel(const int32_t *__restrict__ newc, double *__restrict_
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x)
         totals[e] = decay * totals[e] + (double)newc[e];
-}
-
-__global__ void normalize_kernel(const int32_t *__restrict__ row_off, const int32_t *__restrict__ row_k,
-                                 const double *__restrict__ g, float *__restrict__ cpts,
-                                 int64_t n_rows) {
-#pragma clang fp contract(off)
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rows) return;
-    const int64_t o = row_off[r];
-    const int K = row_k[r];
-    double s = 0.0;
-    for (int k = 0; k < K; ++k) s += g[o + k];
-    for (int k = 0; k < K; ++k) cpts[o + k] = (float)(s > 0.0 ? g[o + k] / s : 1.0 / K);
 }
 
 // ---------------------------------------------------------------- ingest
@@ -2327,15 +2437,6 @@ hipError_t launch_prepare(const DeviceTables &t, const float *cpts, float *table
     return hipGetLastError();
 }
 
-hipError_t launch_moving_sum_gamma(const int32_t *newc, int32_t *mb, int32_t *totals, double alpha, uint32_t key0,
-                                   uint32_t key1, uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                                   hipStream_t stream) {
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dev::moving_sum_gamma_kernel, dim3(blocks_for(total, dev::kBlock)), dim3(dev::kBlock), 0,
-                       stream, newc, mb, totals, alpha, key0, key1, update_id, ids, g, total);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_zero(int32_t *p, int64_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     unsigned nb = blocks_for(count, dev::kBlock);
@@ -2508,25 +2609,35 @@ hipError_t launch_moving_sum(const int32_t *newc, int32_t *mb, int32_t *totals, 
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_gamma_t(const T *totals, double alpha, uint32_t key0, uint32_t key1, uint32_t update_id,
-                          const uint32_t *ids, double *g, int64_t total, hipStream_t stream) {
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dev::gamma_kernel<T>, dim3(blocks_for(total, dev::kBlock)), dim3(dev::kBlock), 0, stream,
-                       totals, alpha, key0, key1, update_id, ids, g, total);
+namespace {
+template <typename T, bool MOVING>
+hipError_t resample(const DeviceTables &t, const int32_t *newc, int32_t *mb, T *totals, const GammaArgs &a,
+                    float *cpts, hipStream_t stream) {
+    if (t.n_tiles > 0)
+        hipLaunchKernelGGL((dev::resample_kernel<T, MOVING>), dim3((unsigned)t.n_tiles), dim3(dev::kResampleBlock),
+                           0, stream, t.tile_row, t.row_off, t.row_k, newc, mb, totals, a.alpha, a.key0, a.key1,
+                           a.update_id, a.ids, cpts);
+    if (t.n_long > 0)
+        hipLaunchKernelGGL((dev::resample_long_kernel<T, MOVING>), dim3((unsigned)t.n_long),
+                           dim3(dev::kResampleBlock), 0, stream, t.long_row, t.row_off, t.row_k, newc, mb, totals,
+                           a.alpha, a.key0, a.key1, a.update_id, a.ids, a.g, cpts);
     return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_gamma(const int32_t *totals, double alpha, uint32_t key0, uint32_t key1,
-                        uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                        hipStream_t stream) {
-    return launch_gamma_t(totals, alpha, key0, key1, update_id, ids, g, total, stream);
+hipError_t launch_resample(const DeviceTables &t, const int32_t *totals, const GammaArgs &a, float *cpts,
+                           hipStream_t stream) {
+    return resample<const int32_t, false>(t, nullptr, nullptr, totals, a, cpts, stream);
 }
 
-hipError_t launch_gamma(const double *totals, double alpha, uint32_t key0, uint32_t key1,
-                        uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                        hipStream_t stream) {
-    return launch_gamma_t(totals, alpha, key0, key1, update_id, ids, g, total, stream);
+hipError_t launch_resample(const DeviceTables &t, const double *totals, const GammaArgs &a, float *cpts,
+                           hipStream_t stream) {
+    return resample<const double, false>(t, nullptr, nullptr, totals, a, cpts, stream);
+}
+
+hipError_t launch_moving_resample(const DeviceTables &t, const int32_t *newc, int32_t *mb, int32_t *totals,
+                                  const GammaArgs &a, float *cpts, hipStream_t stream) {
+    return resample<int32_t, true>(t, newc, mb, totals, a, cpts, stream);
 }
 
 hipError_t launch_advance_ids(uint32_t *ids, uint32_t d0, uint32_t d1, hipStream_t stream) {
@@ -2539,14 +2650,6 @@ hipError_t launch_ema(const int32_t *newc, double *totals, double decay, int64_t
     unsigned nb = blocks_for(total, dev::kBlock);
     if (nb > 4096) nb = 4096;
     hipLaunchKernelGGL(dev::ema_kernel, dim3(nb), dim3(dev::kBlock), 0, stream, newc, totals, decay, total);
-    return hipGetLastError();
-}
-
-hipError_t launch_normalize(const DeviceTables &t, const double *g, float *cpts, int64_t n_rows,
-                            hipStream_t stream) {
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(dev::normalize_kernel, dim3(blocks_for(n_rows, dev::kBlock)), dim3(dev::kBlock),
-                       0, stream, t.row_off, t.row_k, g, cpts, n_rows);
     return hipGetLastError();
 }
 

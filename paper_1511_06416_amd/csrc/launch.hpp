@@ -25,6 +25,9 @@ struct DeviceTables {
     int32_t n_build_blocks = 0;
     int32_t *row_off = nullptr;    // [n_rows]
     int32_t *row_k = nullptr;      // [n_rows]
+    int32_t *tile_row = nullptr;   // [n_tiles] (first row, rows) of each resample tile
+    int32_t *long_row = nullptr;   // [n_long] rows longer than a tile
+    int32_t n_tiles = 0, n_long = 0;
     int32_t *cprog = nullptr;      // threshold build programs
     int32_t *cprog_off = nullptr;
     int32_t *cblk_prog = nullptr;  // threshold-build block -> program
@@ -138,27 +141,31 @@ hipError_t launch_grow(const void *src, int32_t m, void *dst, int32_t m2, int32_
 hipError_t launch_moving_sum(const int32_t *newc, int32_t *mb, int32_t *totals, int64_t total,
                              hipStream_t stream);
 
-// ids (nullable): the update id is read from ids[1] on the device instead.
-hipError_t launch_gamma(const int32_t *totals, double alpha, uint32_t key0, uint32_t key1,
-                        uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                        hipStream_t stream);
-hipError_t launch_gamma(const double *totals, double alpha, uint32_t key0, uint32_t key1,
-                        uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                        hipStream_t stream);
+// The Gamma draws of a resample: g is the scratch of rows longer than a tile
+// (cpt_total doubles); ids (nullable): the update id is read from ids[1] on
+// the device instead.
+struct GammaArgs {
+    double alpha;
+    uint32_t key0, key1, update_id;
+    const uint32_t *ids;
+    double *g;
+};
 
-// launch_moving_sum (totals non-null) followed by launch_gamma on the
+// Every CPT row ~ Dirichlet(alpha + totals).
+hipError_t launch_resample(const DeviceTables &t, const int32_t *totals, const GammaArgs &a, float *cpts,
+                           hipStream_t stream);
+hipError_t launch_resample(const DeviceTables &t, const double *totals, const GammaArgs &a, float *cpts,
+                           hipStream_t stream);
+
+// launch_moving_sum (totals non-null) followed by launch_resample from the
 // updated totals, in one launch.
-hipError_t launch_moving_sum_gamma(const int32_t *newc, int32_t *mb, int32_t *totals, double alpha, uint32_t key0,
-                                   uint32_t key1, uint32_t update_id, const uint32_t *ids, double *g, int64_t total,
-                                   hipStream_t stream);
+hipError_t launch_moving_resample(const DeviceTables &t, const int32_t *newc, int32_t *mb, int32_t *totals,
+                                  const GammaArgs &a, float *cpts, hipStream_t stream);
 
 // ids[0] += d0, ids[1] += d1 (one thread; the last node of a graphed step).
 hipError_t launch_advance_ids(uint32_t *ids, uint32_t d0, uint32_t d1, hipStream_t stream);
 
 // Exponential moving sum: totals = decay * totals + newc (fp64).
 hipError_t launch_ema(const int32_t *newc, double *totals, double decay, int64_t total, hipStream_t stream);
-
-hipError_t launch_normalize(const DeviceTables &t, const double *g, float *cpts, int64_t n_rows,
-                            hipStream_t stream);
 
 }  // namespace same

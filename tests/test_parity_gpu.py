@@ -424,6 +424,27 @@ def test_dirichlet_matches_oracle(cfg, alpha):
     assert rel <= 1e-6
 
 
+@pytest.mark.parametrize("alpha", [1.0, 0.3])
+@pytest.mark.parametrize("card", [[256], [255, 2, 3], [257, 2], [2, 700, 128, 128, 129], [3] * 86])
+def test_dirichlet_tiles(card, alpha):
+    """A resample block takes whole rows of at most 256 entries, or one longer
+    row in pieces: rows that fill a tile, that miss it by one entry, that need
+    two and three pieces; shapes below one."""
+    parents = [[]] * (len(card) - 1) + [[0] if len(card) > 1 else []]
+    net = Network("custom", parents, np.array(card, dtype=np.int32))
+    ctx = H.context_for(net, prior=alpha)
+    totals = np.random.default_rng(len(card)).integers(0, 40, ctx.cpt_total).astype(np.int32)
+    totals[::3] = 0
+    out = torch.empty(ctx.cpt_total, dtype=torch.float32, device="cuda")
+    same.same_sample_cpts(ctx, torch.from_numpy(totals).cuda(), out, 99, 7, ctx.new_workspace())
+    torch.cuda.synchronize()
+    want = oracle.dirichlet(net.parents, net.card, totals, alpha, 99, 7)
+    got = out.cpu().numpy()
+    # bit-equal but for the last bit of the fp64 functions: one entry in 1e5,
+    # which in networks this small is none
+    assert np.array_equal(got, want)
+
+
 # ------------------------------------------------------------ whole loop, lockstep
 
 @pytest.mark.parametrize("cfg,kw,sweeps", [(1, {}, 20), (2, dict(n_cols=6_000, nb=2_000), 3),
