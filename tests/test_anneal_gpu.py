@@ -60,3 +60,35 @@ def test_grow_replicas_4bit(m, m2):
     torch.cuda.synchronize()
     assert np.array_equal(H.from_device(ctx, dst, m2), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("bits", [4, 8, 16])
+@pytest.mark.parametrize("m,m2,ld,shift", [
+    (1, 1, 4, 0),        # one quad, fewer columns than a lane's
+    (4, 13, 2056, 0),    # whole source quads, a second column chunk, 16-byte rows
+    (5, 20, 2052, 0),    # wrapped quads; 4-bit rows that start on 8-byte boundaries
+    (3, 11, 516, 8),     # arrays that start on 8-byte boundaries
+    (6, 9, 260, 2),      # arrays aligned to a 4-bit quad only
+])
+def test_grow_replicas_paths(bits, m, m2, ld, shift):
+    """The widths a lane takes by alignment, over quads that are copied and
+    quads that are assembled from one, two and three source quads."""
+    K = {4: 16, 8: 100, 16: 300}[bits]
+    shift = max(shift, {4: 2, 8: 4, 16: 8}[bits]) if shift else 0
+    ctx = H.context_for(Network("custom", [[], [0]], np.array([K, 3], dtype=np.int32)),
+                        state_bits=4 if bits == 4 else 0)
+    st = np.random.default_rng(m2).integers(0, 3, (2, m, ld)).astype(np.int16 if bits == 16 else np.int8)
+    src = H.to_device(ctx, st)
+
+    def place(t):  # the same tensor at an address `shift` bytes past an aligned one
+        raw = torch.empty(t.numel() * t.element_size() + 64, dtype=torch.uint8, device="cuda")
+        out = raw[shift:shift + t.numel() * t.element_size()].view(t.dtype).view(t.shape)
+        return out.copy_(t)
+
+    src = place(src)
+    shape = same.state_shape(2, m2, ld, 4 if bits == 4 else bits)
+    dst = place(torch.full(shape, -1, dtype=src.dtype, device="cuda"))
+    same.same_grow_replicas(ctx, src, m, dst, m2, ld)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.from_device(ctx, dst, 4 * ((m2 + 3) // 4))[:, :m2], oracle.grow_replicas(st, m2))
+    ctx.close()
