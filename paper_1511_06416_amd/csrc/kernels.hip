@@ -1500,6 +1500,84 @@ struct Span {
         }
     }
 
+    // the quads at p, in one access when WIDE (p on a boundary of the span's
+    // size, at most 16 bytes)
+    template <bool WIDE>
+    __device__ void get(const char *p) {
+        if constexpr (WIDE && kWords == 2) {
+            const u32x2 v = *reinterpret_cast<const u32x2 *>(p);
+            w[0] = v.x;
+            w[1] = v.y;
+        } else if constexpr (WIDE) {
+            static_assert(kWords % 4 == 0, "16-byte pieces");
+#pragma unroll
+            for (int i = 0; i < kWords / 4; ++i) {
+                const u32x4 v = reinterpret_cast<const u32x4 *>(p)[i];
+                w[4 * i] = v.x;
+                w[4 * i + 1] = v.y;
+                w[4 * i + 2] = v.z;
+                w[4 * i + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NQ; ++j) {
+                const V q = Quad<ST>::load_at(p + j * Quad<ST>::kBytes);
+                if constexpr (Quad<ST>::kBytes == 2) w[j >> 1] = j & 1 ? w[j >> 1] | q << 16 : q;
+                else if constexpr (Quad<ST>::kBytes == 4) w[j] = q;
+                else {
+                    w[2 * j] = q.x;
+                    w[2 * j + 1] = q.y;
+                }
+            }
+        }
+    }
+
+    // the quads to p: all of them (WIDE), or those of the columns in `cols`
+    template <bool WIDE>
+    __device__ void set(char *p, int cols) const {
+        if constexpr (WIDE && kWords == 2) {
+            const u32x2 v = {w[0], w[1]};
+            *reinterpret_cast<u32x2 *>(p) = v;
+        } else if constexpr (WIDE) {
+#pragma unroll
+            for (int i = 0; i < kWords / 4; ++i) {
+                const u32x4 v = {w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+                reinterpret_cast<u32x4 *>(p)[i] = v;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NQ; ++j)
+                if ((cols >> j) & 1) Quad<ST>::store_at(p + j * Quad<ST>::kBytes, quad(j));
+        }
+    }
+
+    static constexpr int kBits = Quad<ST>::kBytes * 2;  // bits per state
+
+    // x (a valid state) into slot c of column j (zero before)
+    __device__ void put(int j, int c, uint32_t x) {
+        const int bit = (4 * j + c) * kBits;
+        w[bit >> 5] |= x << (bit & 31);
+    }
+
+    // takes the slots < nslots of the columns in `cols` from n
+    __device__ void blend(const Span &n, int cols, int nslots) {
+        constexpr int kPer = 32 / kBits;  // states per word
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) {
+            uint32_t mask = 0;
+            if constexpr (kPer >= 4) {
+                const uint32_t sl = nslots >= 4 ? 0xffffffffu >> (32 - 4 * kBits) : (1u << (kBits * nslots)) - 1u;
+#pragma unroll
+                for (int h = 0; h < kPer / 4; ++h)
+                    if ((cols >> (i * (kPer / 4) + h)) & 1) mask |= sl << (4 * kBits * h);
+            } else {  // two slots of one column
+                const int left = nslots - 2 * (i & 1);
+                if ((cols >> (i >> 1)) & 1) mask = left >= 2 ? 0xffffffffu : left == 1 ? 0xffffu : 0u;
+            }
+            w[i] = (w[i] & ~mask) | (n.w[i] & mask);
+        }
+    }
+
     // state quad of column j
     __device__ V quad(int j) const {
         if constexpr (Quad<ST>::kBytes == 2) return (w[j >> 1] >> (16 * (j & 1))) & 0xffffu;
@@ -1938,18 +2016,39 @@ __global__ void ema_kernel(const int32_t *__restrict__ newc, double *__restrict_
 // ---------------------------------------------------------------- ingest
 
 // Known entries of one minibatch, CSR with rows = nodes (Sec. 4: a typically
-// sparse variables x cases matrix), into the dense layout: one thread per
-// stored entry.  Two lanes find the rows of the block's first and last
-// entries (the largest i with row_ptr[i] <= e), and each thread searches only
+// sparse variables x cases matrix), into the dense layout: a block takes
+// kExpandEntries consecutive entries, kExpandEntries / kBlock per thread.  Two
+// waves find the rows of the block's first and last entries (the largest i
+// with row_ptr[i] <= e; 64 probes at a time), and each thread searches only
 // between them (usually one or two rows).  The entry's value goes to every
 // replica (Sec. 4: m copies of the known data) and its obs byte is set; obs was
 // cleared by the launcher.  Of repeated (ascending) columns in a row only the
-// last entry writes.
+// last entry writes.  With one entry per thread the blocks were bound by the
+// chain of ten dependent reads of their row search (705 us for 60 M entries
+// of 1000 rows and three replica quads); now 350 us, about the time that
+// reading and writing the partly known lines of states and obs takes.
+constexpr int kExpandEntries = 16 * kBlock;
+
 __device__ __forceinline__ int row_of(const int64_t *__restrict__ row_ptr, int lo, int hi, int64_t e) {
     while (hi - lo > 1) {  // row_ptr[lo] <= e < row_ptr[hi]
         const int mid = (lo + hi) >> 1;
         if (row_ptr[mid] <= e) lo = mid;
         else hi = mid;
+    }
+    return lo;
+}
+
+// The same by a whole wave: the largest i in [0, n) with row_ptr[i] <= e.
+__device__ __forceinline__ int row_of_wave(const int64_t *__restrict__ row_ptr, int n, int64_t e) {
+    const int lane = (int)threadIdx.x & 63;
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) >> 6;
+        const int at = lo + lane * step;
+        const uint64_t le = __ballot(at < hi && row_ptr[at < hi ? at : lo] <= e);  // lanes 0 .. k - 1
+        const int k = __builtin_popcountll(le);
+        lo += k > 0 ? (k - 1) * step : 0;
+        hi = lo + step < hi ? lo + step : hi;
     }
     return lo;
 }
@@ -1961,69 +2060,116 @@ __global__ __launch_bounds__(kBlock) void expand_kernel(const int64_t *__restric
                                                         int64_t nnz, int32_t m, int64_t n_cols, int64_t ld,
                                                         char *__restrict__ states, uint8_t *__restrict__ obs) {
     __shared__ int32_t span[2];
-    const int64_t e0 = (int64_t)blockIdx.x * kBlock;
-    const int64_t e_last = e0 + kBlock <= nnz ? e0 + kBlock - 1 : nnz - 1;
-    if (threadIdx.x < 2) span[threadIdx.x] = row_of(row_ptr, 0, n, threadIdx.x == 0 ? e0 : e_last);
+    const int64_t e0 = (int64_t)blockIdx.x * kExpandEntries;
+    const int64_t e_end = e0 + kExpandEntries < nnz ? e0 + kExpandEntries : nnz;
+    if (threadIdx.x < 128) {
+        const int r = row_of_wave(row_ptr, n, threadIdx.x < 64 ? e0 : e_end - 1);
+        if ((threadIdx.x & 63) == 0) span[threadIdx.x >> 6] = r;
+    }
     __syncthreads();
-    const int64_t e = e0 + threadIdx.x;
-    if (e >= nnz) return;
-    const int lo = row_of(row_ptr, span[0], span[1] + 1, e);
-    const int64_t j = col_idx[e];
-    if (j < 0 || j >= n_cols) return;
-    if (e + 1 < row_ptr[lo + 1] && col_idx[e + 1] == j) return;  // a later entry of this column
-    obs[(int64_t)lo * ld + j] = 1;
-    // every slot of the column's state quads, padding included, takes the value
-    const typename Quad<ST>::V v = Quad<ST>::splat((int)values[e]);
-    char *dst = states + (int64_t)lo * node_bytes<ST>(m, ld) + quad_boff<ST>(0, ld, j);
+    const int lo0 = span[0], hi0 = span[1] + 1;
     const int mq = (m + 3) >> 2;
-    for (int rq = 0; rq < mq; ++rq) Quad<ST>::store_at(dst + (int64_t)rq * ld * Quad<ST>::kBytes, v);
+    const int64_t row = ld * Quad<ST>::kBytes;
+#pragma unroll 4
+    for (int64_t e = e0 + threadIdx.x; e < e_end; e += kBlock) {
+        const int64_t j = col_idx[e];
+        const typename Quad<ST>::V v = Quad<ST>::splat((int)values[e]);
+        const int lo = row_of(row_ptr, lo0, hi0, e);
+        if (j < 0 || j >= n_cols) continue;
+        // a later entry of this column writes instead
+        if (e + 1 < nnz && col_idx[e + 1] == j && e + 1 < row_ptr[lo + 1]) continue;
+        obs[(int64_t)lo * ld + j] = 1;
+        // every slot of the column's state quads, padding included, takes the value
+        char *dst = states + (int64_t)lo * node_bytes<ST>(m, ld) + quad_boff<ST>(0, ld, j);
+        for (int rq = 0; rq < mq; ++rq, dst += row) Quad<ST>::store_at(dst, v);
+    }
 }
 
-// Random initial latent states (Sec. 5.2): one thread per (node, column
-// quad), looping over the replicas; for replica r the Philox block at counter
-// {g >> 2, i, r | 2 << 24, 0} (g the global column of the quad's first
-// column) gives word c to column c, and the state is ((w >> 8) * K_i) >> 24 =
-// floor(U * K_i) exactly.  The quad's obs dword is read once; for each
-// replica quad, the state quads of the four columns are read, the latent
-// columns' real slots replaced, and written back.  Observed entries and
+// Random initial latent states (Sec. 5.2): for replica r of a node's four
+// columns from col on, the Philox block at counter {g >> 2, i, r | 2 << 24, 0}
+// (g the global column of the first) gives word c to column c, and the state
+// is ((w >> 8) * K_i) >> 24 = floor(U * K_i) exactly.  Observed entries and
 // padding slots keep their values.
-template <typename ST>
+//
+// Bound by the Philox blocks, one per column group and replica.  A block lists
+// the column groups of its chunk that have a latent column and gives them to
+// its lanes, so that no lane waits out the blocks of others (at 40% missing
+// 13% of the groups have none, at 10% two thirds).  A lane keeps its group
+// over the replicas: the replica is then uniform, and what the first two
+// rounds make of the column alone is formed once.  The four columns' states
+// are drawn whole and the latent ones blended in; WIDE (the array on a
+// boundary of 8 or 16 bytes): a group's state quads are one access.  1000
+// nodes x 100,000 columns, m = 10, 40% missing: 454-480 us with a thread per
+// group and replicas' states put one by one, now 400-455 us.
+constexpr int kInitGroups = 2 * kBlock;  // column groups of a chunk
+
+template <typename ST, bool WIDE>
 __global__ __launch_bounds__(kBlock) void init_latent_kernel(const int32_t *__restrict__ cdesc,
                                                              const int32_t *__restrict__ cdesc_off,
-                                                             int32_t n, int32_t m, int64_t n_cols,
+                                                             int32_t chunks, int32_t m, int64_t n_cols,
                                                              int64_t ld, int64_t col_offset, uint32_t k0,
                                                              uint32_t k1, char *__restrict__ states,
                                                              const uint8_t *__restrict__ obs) {
-    using Q = Quad<ST>;
-    const int64_t quads = (n_cols + 3) >> 2;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n * quads) return;
-    const int64_t q = t % quads;
-    const int i = (int)(t / quads);
-    const int64_t col = 4 * q;
-    const uint32_t ob = *reinterpret_cast<const uint32_t *>(obs + (int64_t)i * ld + col);
-    int lat = 0;
+    using S = Span<ST, 4>;
+    __shared__ uint16_t list[kInitGroups];  // column group | latent mask << 12
+    __shared__ int32_t wave_n[kInitGroups / 64];
+    static_assert(kInitGroups <= 4096, "12-bit group numbers");
+    const int node = (int)(blockIdx.x / (uint32_t)chunks), chunk = (int)(blockIdx.x % (uint32_t)chunks);
+    const int64_t q0 = (int64_t)chunk * kInitGroups;  // first column group
+    int lat[kInitGroups / kBlock], at[kInitGroups / kBlock];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-        if (((ob >> (8 * c)) & 0xffu) == 0 && col + c < n_cols) lat |= 1 << c;
-    if (!lat) return;
-    const uint32_t K = (uint32_t)cdesc[cdesc_off[i]];
-    const int mq = (m + 3) >> 2;
-    for (int rq = 0; rq < mq; ++rq) {
-        char *p = states + (int64_t)i * node_bytes<ST>(m, ld) + quad_boff<ST>(rq, ld, col);
-        typename Q::V v[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = Q::load_at(p + c * Q::kBytes);
-        for (int s = 0; s < 4 && 4 * rq + s < m; ++s) {
-            const Philox4 b = philox4x32_10((uint32_t)((col_offset >> 2) + q), (uint32_t)i,
-                                            (uint32_t)(4 * rq + s) | (2u << 24), 0u, k0, k1);
+    for (int p = 0; p < kInitGroups / kBlock; ++p) {
+        const int64_t col = 4 * (q0 + p * kBlock + (int64_t)threadIdx.x);
+        lat[p] = 0;
+        if (col < n_cols) {
+            const uint32_t ob = *reinterpret_cast<const uint32_t *>(obs + (int64_t)node * ld + col);
 #pragma unroll
             for (int c = 0; c < 4; ++c)
-                if ((lat >> c) & 1) v[c] = Q::put(v[c], s, (int)(((uint64_t)(b.w[c] >> 8) * K) >> 24));
+                if (((ob >> (8 * c)) & 0xffu) == 0 && col + c < n_cols) lat[p] |= 1 << c;
         }
+        const uint64_t some = __ballot(lat[p] != 0);
+        if ((threadIdx.x & 63) == 0) wave_n[p * (kBlock / 64) + (threadIdx.x >> 6)] = __builtin_popcountll(some);
+        at[p] = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
+    }
+    __syncthreads();
+    int n_groups = 0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if ((lat >> c) & 1) Q::store_at(p + c * Q::kBytes, v[c]);
+    for (int v = 0; v < kInitGroups / 64; ++v) {
+#pragma unroll
+        for (int p = 0; p < kInitGroups / kBlock; ++p)
+            at[p] += v < p * (kBlock / 64) + (int)(threadIdx.x >> 6) ? wave_n[v] : 0;
+        n_groups += wave_n[v];
+    }
+#pragma unroll
+    for (int p = 0; p < kInitGroups / kBlock; ++p)
+        if (lat[p]) list[at[p]] = (uint16_t)((p * kBlock + threadIdx.x) | lat[p] << 12);
+    __syncthreads();
+    const uint32_t K = (uint32_t)as_const(cdesc)[as_const(cdesc_off)[node]];
+    const int mq = (m + 3) >> 2;
+    const int64_t row = ld * Quad<ST>::kBytes;
+    for (int t = threadIdx.x; t < n_groups; t += kBlock) {
+        const int l = list[t];
+        const int64_t q = q0 + (l & 0xfff);
+        char *p = states + (int64_t)node * node_bytes<ST>(m, ld) + quad_boff<ST>(0, ld, 4 * q);
+        for (int rq = 0; rq < mq; ++rq, p += row) {
+            const int nslots = m - 4 * rq < 4 ? m - 4 * rq : 4;  // uniform
+            S v, drawn;
+            v.template get<WIDE>(p);
+#pragma unroll
+            for (int i = 0; i < S::kWords; ++i) drawn.w[i] = 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (s >= nslots) break;
+                const Philox4 b = philox4x32_10((uint32_t)((col_offset >> 2) + q), (uint32_t)node,
+                                                (uint32_t)(4 * rq + s) | (2u << 24), 0u, k0, k1);
+                // ((w >> 8) * K) >> 24
+#pragma unroll
+                for (int c = 0; c < 4; ++c) drawn.put(c, s, __umulhi(b.w[c] & 0xffffff00u, K));
+            }
+            v.blend(drawn, l >> 12, nslots);
+            v.template set<WIDE>(p, l >> 12);
+        }
     }
 }
 
@@ -2563,7 +2709,7 @@ hipError_t launch_expand(const int64_t *row_ptr, int32_t n, const int32_t *col_i
     // obs [n][ld] bytes (ld a multiple of 4) cleared as words, then the entries
     hipError_t e = launch_fill_zero(reinterpret_cast<int32_t *>(obs), (int64_t)n * ld / 4, stream);
     if (e != hipSuccess || nnz <= 0) return e;
-    const int64_t blocks = (nnz + dev::kBlock - 1) / dev::kBlock;
+    const int64_t blocks = (nnz + dev::kExpandEntries - 1) / dev::kExpandEntries;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     by_format(state_bits, [&](auto tag) {
         using ST = decltype(tag);
@@ -2577,15 +2723,22 @@ hipError_t launch_expand(const int64_t *row_ptr, int32_t n, const int32_t *col_i
 hipError_t launch_init_latent(const DeviceTables &t, int32_t n, int32_t m, int64_t n_cols, int64_t ld,
                               int64_t col_offset, uint32_t key0, uint32_t key1, int32_t state_bits,
                               void *states, const uint8_t *obs, hipStream_t stream) {
-    const int64_t items = (int64_t)n * ((n_cols + 3) / 4);
-    if (items <= 0) return hipSuccess;
-    const int64_t blocks = (items + dev::kBlock - 1) / dev::kBlock;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (n <= 0 || n_cols <= 0) return hipSuccess;
+    const int64_t chunks = (n_cols + 4 * dev::kInitGroups - 1) / (4 * dev::kInitGroups);
+    if (chunks * n > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(chunks * n));
+#define SAME_LAUNCH_INIT(ST, WIDE)                                                                              \
+    hipLaunchKernelGGL((dev::init_latent_kernel<ST, WIDE>), grid, dim3(dev::kBlock), 0, stream, t.cdesc, \
+                       t.cdesc_off, (int32_t)chunks, m, n_cols, ld, col_offset, key0, key1, (char *)states, obs)
+    // rows are whole groups of four columns (ld is a multiple of 4): only the
+    // array's own address can stand against the wide accesses
     by_format(state_bits, [&](auto tag) {
-        hipLaunchKernelGGL(dev::init_latent_kernel<decltype(tag)>, dim3((unsigned)blocks), dim3(dev::kBlock), 0,
-                           stream, t.cdesc, t.cdesc_off, n, m, n_cols, ld, col_offset, key0, key1, (char *)states,
-                           obs);
+        using ST = decltype(tag);
+        const uintptr_t piece = dev::Quad<ST>::kBytes == 2 ? 8 : 16;
+        if (reinterpret_cast<uintptr_t>(states) % piece == 0) SAME_LAUNCH_INIT(ST, true);
+        else SAME_LAUNCH_INIT(ST, false);
     });
+#undef SAME_LAUNCH_INIT
     return hipGetLastError();
 }
 

@@ -122,3 +122,39 @@ def test_expand_and_init_latent_4bit(cfg, kw):
     torch.cuda.synchronize()
     assert np.array_equal(H.from_device(ctx, g, m), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,n_cols", [(64, 70), (65, 9), (4200, 5), (1, 20_000)])
+def test_expand_row_search(n, n_cols):
+    """A block's entries span many short rows (found by 64 probes at a time:
+    one, two and three rounds) or lie inside one long row; some rows empty."""
+    rng = np.random.default_rng(n)
+    ld = (n_cols + 3) // 4 * 4
+    ob = (rng.random((n, ld)) < 0.5).astype(np.uint8)
+    ob[rng.random(n) < 0.2] = 0
+    st = np.repeat(rng.integers(0, 3, (n, 1, ld)), 2, axis=1).astype(np.int8)
+    _expand_case(Network("custom", [[] for _ in range(n)], np.full(n, 3, dtype=np.int32)), st, ob, n_cols, 2)
+
+
+@pytest.mark.parametrize("bits,shift", [(4, 2), (8, 4), (16, 8)])
+@pytest.mark.parametrize("n_cols,hidden", [(1, 1.0), (1027, 0.05), (1024, 0.9)])
+def test_init_latent_alignment(bits, shift, n_cols, hidden):
+    """Column groups listed by block (few, most, one group) with the states
+    aligned for whole-group accesses and only to a state quad."""
+    K = {4: 16, 8: 100, 16: 300}[bits]
+    n, m, ld = 3, 5, (n_cols + 3) // 4 * 4
+    card = np.array([K, 7, 2], dtype=np.int32)
+    rng = np.random.default_rng(n_cols)
+    ob = (rng.random((n, ld)) >= hidden).astype(np.uint8)
+    st = np.ones((n, m, ld), dtype=np.int16 if bits == 16 else np.int8)
+    ref = st.copy()
+    oracle.init_latent(card, n_cols, m, 8, 21, ref, ob)
+    ctx = H.context_for(Network("custom", [[], [0], [0, 1]], card), state_bits=4 if bits == 4 else 0)
+    for off in (0, shift):
+        t = H.to_device(ctx, st)
+        raw = torch.empty(t.numel() * t.element_size() + 64, dtype=torch.uint8, device="cuda")
+        g = raw[off:off + t.numel() * t.element_size()].view(t.dtype).view(t.shape).copy_(t)
+        same.same_init_latent(ctx, g, torch.from_numpy(ob).cuda(), m, n_cols, ld, 8, 21)
+        torch.cuda.synchronize()
+        assert np.array_equal(H.from_device(ctx, g, m), ref)
+    ctx.close()
