@@ -32,6 +32,11 @@ constexpr int kBlock = 256;          // 4 wavefronts of 64
 constexpr int kSweepBlock = 256;     // threads of a sweep block
 constexpr int kSweepWaves = 6;       // waves per SIMD the fast sweep kernel is compiled for
 
+// Global-memory bytes (address space 1) from a scalar base: with a scalar
+// base and a 32-bit vector offset computed in the same block, the loads take
+// the scalar-base form (no 64-bit vector address arithmetic).
+typedef const __attribute__((address_space(1))) char global_char;
+
 // ---------------------------------------------------------------- state quads
 //
 // States are stored as replica quads: states[n][mq][ld][4] with mq = ceil(m/4),
@@ -72,6 +77,9 @@ struct Quad<int8_t> {
     __device__ static V load_buffer(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
         return __builtin_amdgcn_raw_buffer_load_b32(r, (int)boff, 0, 0);
     }
+    __device__ static V load_global(global_char *row, uint32_t boff) {
+        return *reinterpret_cast<const __attribute__((address_space(1))) uint32_t *>(row + boff);
+    }
     __device__ static void store(int8_t *p, V v) { *reinterpret_cast<uint32_t *>(p) = v; }
     __device__ static void store_buffer(__amdgpu_buffer_rsrc_t r, uint32_t boff, V v) {
         __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)boff, 0, 0);
@@ -107,6 +115,11 @@ struct Quad<int16_t> {
     __device__ static V load_buffer(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
         typedef uint32_t w2 __attribute__((ext_vector_type(2)));
         const w2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)boff, 0, 0);
+        return make_uint2(v.x, v.y);
+    }
+    __device__ static V load_global(global_char *row, uint32_t boff) {
+        typedef uint32_t w2 __attribute__((ext_vector_type(2)));
+        const w2 v = *reinterpret_cast<const __attribute__((address_space(1))) w2 *>(row + boff);
         return make_uint2(v.x, v.y);
     }
     __device__ static void store(int16_t *p, V v) { *reinterpret_cast<uint2 *>(p) = v; }
@@ -157,6 +170,9 @@ struct Quad<Nib> {
     __device__ static void store_at(char *p, V v) { *reinterpret_cast<uint16_t *>(p) = (uint16_t)v; }
     __device__ static V load_buffer(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
         return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)boff, 0, 0);
+    }
+    __device__ static V load_global(global_char *row, uint32_t boff) {
+        return *reinterpret_cast<const __attribute__((address_space(1))) uint16_t *>(row + boff);
     }
     __device__ static void store_buffer(__amdgpu_buffer_rsrc_t r, uint32_t boff, V v) {
         __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)boff, 0, 0);
@@ -315,11 +331,6 @@ __device__ __forceinline__ void read_kvec_lds(lds_char *p, float (&f)[KP]) {
 }
 
 constexpr int log2i(int v) { return v <= 1 ? 0 : 1 + log2i(v / 2); }
-
-// Global-memory bytes (address space 1) from a scalar base: with a scalar
-// base and a 32-bit vector offset computed in the same block, the loads take
-// the scalar-base form (no 64-bit vector address arithmetic).
-typedef const __attribute__((address_space(1))) char global_char;
 
 __device__ __forceinline__ global_char *scalar_global_ptr(const void *p) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);
@@ -924,15 +935,91 @@ __device__ __forceinline__ void read_thresholds(bool from_lds, lds_char *lds, gl
     }
 }
 
+// The draws of an item from its configuration index: the drawn state of a
+// slot is the number of its KT thresholds at or below the 24-bit uniform.
+template <int KT, typename ST>
+__device__ __forceinline__ typename Quad<ST>::V table_draws(bool tab_lds, lds_char *lds, global_char *gcond,
+                                                            const uint32_t (&Pk)[2], const Philox4 &rnd) {
+    typename Quad<ST>::V out{};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t u24 = rnd.w[c] >> 8;
+        uint32_t th[KT];
+        read_thresholds<KT>(tab_lds, lds, gcond, packed_index<ST>(Pk, c), th);
+        int pick = 0;
+#pragma unroll
+        for (int k = 0; k < KT; ++k) pick += th[k] <= u24 ? 1 : 0;
+        out = Quad<ST>::put(out, c, pick);
+    }
+    return out;
+}
+
+// Threshold path for a blanket of N nodes, thresholds staged in LDS: the
+// blanket rows' addresses and multipliers stay in scalar registers over the
+// block's items, so an item is straight-line code whose N state quads are in
+// flight together.  (The walk over the descriptor's list costs about 100
+// scalar instructions, a branch and a scalar load per item and batch: as much
+// issue time as the draws.)
+template <int KT, int N, typename ST>
+__device__ __forceinline__ void sweep_table_rows(const SweepParams &P, const Work &W, const Items &I, lds_char *lds,
+                                                 cint32_t *grp) {
+    using Q = Quad<ST>;
+    char *states = reinterpret_cast<char *>(P.states);
+    const int64_t vstride = node_bytes<ST>(P.m, P.ld);
+    const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
+    global_char *row[N];
+    uint32_t mult[N];
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        row[t] = scalar_global_ptr(states + (uint64_t)(uint32_t)grp[2 + 2 * t] * (uint32_t)vstride);
+        mult[t] = (uint32_t)grp[3 + 2 * t];
+    }
+    const uint32_t base = (uint32_t)grp[1];
+    const int n_items = I.ncl * I.nrq;
+    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
+        int64_t j;
+        int rb, nrep;
+        item_of(I, t, j, rb, nrep);
+        const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
+        typename Q::V v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = Q::load_global(row[i], qoff);
+        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
+        uint32_t Pk[2] = {base, base};
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            uint32_t p[2];
+            Q::split(Q::keep(v[i], nrep), p);
+            Pk[0] = pk_mad_u16(p[0], mult[i], Pk[0]);
+            Pk[1] = pk_mad_u16(p[1], mult[i], Pk[1]);
+        }
+        Q::store_buffer(own, qoff, table_draws<KT, ST>(true, lds, nullptr, Pk, rnd));
+    }
+}
+
 // Threshold path (classes 0 and 1): the blanket configuration of each
-// replica slot selects KT thresholds; the drawn state is the number of them
-// at or below the 24-bit uniform.
+// replica slot selects KT thresholds.
 template <int KT, typename ST, bool DEBUG, bool STAGED>
 __device__ __forceinline__ void sweep_table(const SweepParams &P, const Work &W, const Items &I, lds_char *lds,
                                             global_char *gcond) {
     cint32_t *d = W.d;
     cint32_t *grp = d + d[9];
     const bool tab_lds = STAGED && d[13] > 0;  // uniform: thresholds staged in LDS
+    if constexpr (STAGED && !DEBUG) {
+        if (tab_lds) {
+            switch (grp[0]) {  // the blanket's nodes; larger ones walk the list below
+            case 1: return sweep_table_rows<KT, 1, ST>(P, W, I, lds, grp);
+            case 2: return sweep_table_rows<KT, 2, ST>(P, W, I, lds, grp);
+            case 3: return sweep_table_rows<KT, 3, ST>(P, W, I, lds, grp);
+            case 4: return sweep_table_rows<KT, 4, ST>(P, W, I, lds, grp);
+            case 5: return sweep_table_rows<KT, 5, ST>(P, W, I, lds, grp);
+            case 6: return sweep_table_rows<KT, 6, ST>(P, W, I, lds, grp);
+            case 7: return sweep_table_rows<KT, 7, ST>(P, W, I, lds, grp);
+            case 8: return sweep_table_rows<KT, 8, ST>(P, W, I, lds, grp);
+            default: break;
+            }
+        }
+    }
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
@@ -946,18 +1033,7 @@ __device__ __forceinline__ void sweep_table(const SweepParams &P, const Work &W,
         uint32_t Pk[2];
         item_group<ST>(g, states, vstride, qoff, nrep, Pk);
         const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
-        typename Quad<ST>::V out{};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t u24 = rnd.w[c] >> 8;
-            uint32_t th[KT];
-            read_thresholds<KT>(tab_lds, lds, gcond, packed_index<ST>(Pk, c), th);
-            int pick = 0;
-#pragma unroll
-            for (int k = 0; k < KT; ++k) pick += th[k] <= u24 ? 1 : 0;
-            out = Quad<ST>::put(out, c, pick);
-        }
-        Quad<ST>::store_buffer(own, qoff, out);
+        Quad<ST>::store_buffer(own, qoff, table_draws<KT, ST>(tab_lds, lds, gcond, Pk, rnd));
         if (DEBUG) {
             for (int c = 0; c < nrep; ++c) table_debug_prob<ST>(P, W, rb + c, j);
         }
