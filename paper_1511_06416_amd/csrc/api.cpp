@@ -353,7 +353,8 @@ int sweep_tile(same_ctx *ctx, const same::SweepParams &P0, int64_t t0, int64_t n
                 if (!rc) rc = check_hip(hipEventRecord(rec.start, ls), "hipEventRecord");
                 if (rc) return rc;
             }
-            rc = check_hip(same::launch_sweep(P, b, e - b, k, g.launch_lds[c * L + k], g.state_bits, ls),
+            rc = check_hip(same::launch_sweep(P, b, e - b, g.launch_long[c * L + k], k, g.launch_lds[c * L + k],
+                                              g.state_bits, ls),
                            "sweep launch");
             if (rc) return rc;
             if (timed) {

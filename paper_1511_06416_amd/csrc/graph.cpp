@@ -409,7 +409,8 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
         }
         g.klass[i] = klass;
 
-        const int32_t base = (int32_t)g.desc.size();
+        // descriptors on 32-byte boundaries: a record is one scalar load
+        const int32_t base = (int32_t)((g.desc.size() + 7) & ~size_t(7));
         g.desc_off[i] = base;
         g.desc.resize(base + kDescHeader, 0);
         g.desc[base + 0] = K;
@@ -502,7 +503,30 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
                     // staged groups count bytes into LDS, the rest k-vectors
                     ok = ok && emit(gb, (int32_t)t < n_staged ? 1 : unit, true);
                 }
-                if (ok) {
+                size_t most = 0;
+                for (const auto &gr : groups) most = std::max(most, gr.ent.size());
+                if (ok && KP == 2 && (int32_t)groups.size() >= kRecordGroups && most <= 4 &&
+                    n_staged == (int32_t)groups.size()) {
+                    // group records of a fixed number of entries
+                    const int32_t E = most <= 2 ? 2 : 4;
+                    g.desc.resize(base + (((int64_t)g.desc.size() - base + 7) & ~int64_t(7)), 0);
+                    const int64_t at = (int64_t)g.desc.size();
+                    int64_t pos = base + g.desc[base + 9];
+                    for (size_t t = 0; t < groups.size(); ++t) {
+                        const int32_t ne = g.desc[pos], gbase = g.desc[pos + 1];
+                        for (int32_t q = 0; q < E; ++q) {
+                            const int32_t node = q < ne ? g.desc[pos + 2 + 2 * q] : i;
+                            const int32_t mult = q < ne ? g.desc[pos + 3 + 2 * q] : 0;
+                            g.desc.push_back(node);
+                            g.desc.push_back(mult);
+                        }
+                        g.desc.push_back(gbase);
+                        while (((int64_t)g.desc.size() - at) % 8) g.desc.push_back(0);
+                        pos += 2 + 2 * ne;
+                    }
+                    g.desc[base + 6] = (int32_t)(at - base);
+                    g.desc[base + 7] = E;
+                } else if (ok) {
                     // the same list flat: per entry [node, mult, group base,
                     // flags: 1 first of its group, 2 last, 4 staged group];
                     // an empty group is one entry of the node itself with
@@ -575,6 +599,7 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
     // per (colour, class) the LDS bytes the launch needs
     g.launch.assign((size_t)g.n_colors * (kLaunchClasses + 1), 0);
     g.launch_lds.assign((size_t)g.n_colors * kLaunchClasses, 0);
+    g.launch_long.assign((size_t)g.n_colors * kLaunchClasses, 0);
     // a node's sweep cost per item, estimated from its fast list: the
     // entries' loads and, per group, the k-vector products or thresholds
     auto sweep_cost = [&](int32_t i) {
@@ -601,7 +626,10 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
             // the costliest nodes first: their blocks of every column slab
             // start before the cheap ones, which shortens the launch's tail
             std::stable_sort(nodes.begin(), nodes.end());
-            for (const auto &ni : nodes) g.order.push_back(ni.second);
+            for (const auto &ni : nodes) {
+                g.order.push_back(ni.second);
+                if (-ni.first > kLongItem) g.launch_long[c * kLaunchClasses + k] += 1;
+            }
         }
         g.launch[c * (kLaunchClasses + 1) + kLaunchClasses] = (int32_t)g.order.size();
     }

@@ -70,6 +70,12 @@ constexpr int64_t kDefaultLdsBytes = 24576;  // default budget: 6 blocks per CU 
 // budget, so no threshold node gathers from global memory (measured best)
 constexpr int64_t kDefaultTableLimit = kDefaultLdsBytes / 4;
 constexpr int32_t kDescHeader = 16;
+// a node's items are long when their estimated cost (entries plus k-vector or
+// threshold width per group) exceeds this: an item then takes about as long as
+// a block's start (lists, staging), so a small launch rather has more blocks
+// than more items per lane
+constexpr int64_t kLongItem = 16;
+constexpr int32_t kRecordGroups = 4;         // fewest groups that get records (see the descriptor)
 constexpr int64_t kPackedLimit = 65536;      // packed indices are 16-bit
 constexpr int32_t kCountLdsBins = 8192;      // bins of the count kernel's LDS histogram
 constexpr int32_t kResampleTile = 256;       // CPT entries of a resample block
@@ -78,6 +84,9 @@ constexpr int64_t kCountSplitBins = 4 * kCountLdsBins;  // largest CPT counted i
 // Sweep descriptor of a node (int32 words at desc_off[i]):
 //   [0] K  [1] KP  [2] mode  [3] tab_begin  [4] tab_len (floats)
 //   [5] cond_off  [6] cond_len (threshold words)  [7] KT
+//       two-state product nodes with kRecordGroups or more groups, all of them
+//       staged and of at most 4 entries: [6] relative word index of the group
+//       records, [7] entries per record (2 or 4; 0: no records)
 //   [8] n_fast  [9] fast (relative word index of the fast group list)
 //   [10] n_wide [11] wide (relative word index of the wide group list)
 //   [12] launch class
@@ -90,6 +99,10 @@ constexpr int64_t kCountSplitBins = 4 * kCountLdsBins;  // largest CPT counted i
 //        a four-word header [E, 0, 0, 0]: [node, mult, group base, flags]
 //        with flags 1 = first entry of its group, 2 = last, 4 = staged
 //        group; an empty group is one entry of the node itself with mult 0
+//       (nodes without group records)
+// Group records (see [6]): per group of the fast list, in list order, [7]
+// entries (node, mult), missing ones the node itself with mult 0, then the
+// group's base, padded to a multiple of 8 words.
 // A group list is a sequence of groups [n_e, base, (node, mult) * n_e]; the
 // group's index is base + sum of mult * state over its entries.
 //   wide list (every node): group 0 is the node's own row (entries: its
@@ -166,6 +179,7 @@ struct Compiled {
     std::vector<int32_t> order;
     std::vector<int32_t> launch;       // [n_colors * (kLaunchClasses + 1)]
     std::vector<int32_t> launch_lds;   // [n_colors * kLaunchClasses]
+    std::vector<int32_t> launch_long;  // [n_colors * kLaunchClasses] leading nodes with long items (kLongItem)
     std::vector<int32_t> mode;         // [n]
     std::vector<int32_t> klass;        // [n] launch class
 

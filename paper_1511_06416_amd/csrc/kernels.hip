@@ -66,6 +66,12 @@ struct ElemOf<Nib> {
 template <typename ST>
 struct Quad;
 
+// The states of a quad's first slots in the two words of 16-bit lanes that
+// Quad::split makes (the others read as 0); see slot_mask.
+struct SlotMask {
+    uint32_t w[2];
+};
+
 template <>
 struct Quad<int8_t> {
     using V = uint32_t;
@@ -98,6 +104,10 @@ struct Quad<int8_t> {
     __device__ static void split(V v, uint32_t (&p)[2]) {
         p[0] = v & 0x00ff00ffu;
         p[1] = __builtin_amdgcn_perm(0u, v, 0x0c030c01u);
+    }
+    __device__ static void split(V v, const SlotMask &k, uint32_t (&p)[2]) {
+        p[0] = v & k.w[0];
+        p[1] = __builtin_amdgcn_perm(0u, v, 0x0c030c01u) & k.w[1];
     }
     __device__ static constexpr int word_of(int c) { return c & 1; }
     __device__ static constexpr int half_of(int c) { return c >> 1; }
@@ -157,6 +167,10 @@ struct Quad<int16_t> {
         p[0] = v.x;
         p[1] = v.y;
     }
+    __device__ static void split(V v, const SlotMask &k, uint32_t (&p)[2]) {
+        p[0] = v.x & k.w[0];
+        p[1] = v.y & k.w[1];
+    }
     __device__ static constexpr int word_of(int c) { return c >> 1; }
     __device__ static constexpr int half_of(int c) { return c & 1; }
 };
@@ -190,9 +204,26 @@ struct Quad<Nib> {
         p[0] = t & 0x000f000fu;
         p[1] = (t >> 4) & 0x000f000fu;
     }
+    __device__ static void split(V v, const SlotMask &k, uint32_t (&p)[2]) {
+        const uint32_t t = __builtin_amdgcn_perm(0u, v, 0x0c010c00u);
+        p[0] = t & k.w[0];
+        p[1] = (t >> 4) & k.w[1];
+    }
     __device__ static constexpr int word_of(int c) { return c & 1; }
     __device__ static constexpr int half_of(int c) { return c >> 1; }
 };
+
+// Mask of the first nrep (1..4) slots.
+template <typename ST>
+__device__ __forceinline__ SlotMask slot_mask(int nrep) {
+    SlotMask m;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) m.w[i] = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        m.w[Quad<ST>::word_of(c)] |= c < nrep ? Quad<ST>::kMask << (16 * Quad<ST>::half_of(c)) : 0u;
+    return m;
+}
 
 // Bytes of one node's block: mq quads of ld columns.
 template <typename ST>
@@ -434,23 +465,30 @@ __device__ __forceinline__ void running_sums(float (&w)[KP]) {
     for (int k = 1; k < KP; ++k) w[k] += w[k - 1];
 }
 
+// acc with the sign bit of x appended.  Counting sign bits (subtract, append,
+// one bit count at the end) takes two instructions per compared value and no
+// scalar condition between them; a compare, a select and an add take three
+// and wait states.
+__device__ __forceinline__ uint32_t append_sign(uint32_t acc, uint32_t x) {
+    return __builtin_amdgcn_alignbit(acc, x, 31);
+}
+
 // Inverse-CDF draw from running sums S (entries K..KP-1 repeat Z = S_{K-1}):
-// the smallest k with u*Z < S_k, i.e. the number of S_k <= u*Z.  When
-// rounding makes u*Z reach Z, the largest k whose weight is positive (whose
-// running sum grows) is taken.
+// the smallest k with u*Z < S_k, i.e. the number of S_k <= u*Z.  u is at most
+// 1 - 2^-24, so the rounded u*Z stays below Z (the next float below Z is at
+// most Z * 2^-23 away, and a product less than half of that from Z would need
+// u > 1 - 2^-24): the last sum need not be compared.  The product is rounded
+// before it is compared, as the rule has it (no fused subtraction).  (min: a weight that is
+// not finite still gives a valid state.)
 template <int KP>
 __device__ __forceinline__ int draw_sums(const float (&S)[KP], int K, float u) {
+#pragma clang fp contract(off)
     const float t = u * S[KP - 1];
-    int pick = 0;
+    uint32_t below = 0;  // sums above t
 #pragma unroll
-    for (int k = 0; k < KP; ++k) pick += (S[k] <= t) ? 1 : 0;
-    if (pick >= K) {
-        pick = 0;
-#pragma unroll
-        for (int k = 1; k < KP; ++k)
-            if (k < K && S[k] > S[k - 1]) pick = k;
-    }
-    return pick;
+    for (int k = 0; k < KP - 1; ++k) below = append_sign(below, __builtin_bit_cast(uint32_t, t - S[k]));
+    const int pick = KP - 1 - __builtin_popcount(below);
+    return pick < K - 1 ? pick : K - 1;
 }
 
 // Z below this sends the quad through the renormalising walk: Z >= 2^-96
@@ -466,6 +504,7 @@ struct Work {
     cint32_t *d;
     int64_t q0, q1;
     int r0, r1;
+    int quads;  // column quads of a whole chunk
 };
 
 // Blocks are dealt to the XCDs round robin by linear block id.  The 1-D grid
@@ -474,8 +513,10 @@ struct Work {
 // slab: the blocks resident on an XCD then read the same columns of the
 // shared blanket rows, which stay in that XCD's L2.
 constexpr uint32_t kXcds = 8;
-constexpr int kSweepQuadsPerLane = 1;  // column quads per lane in one sweep block
+constexpr int kSweepPasses = 4;  // most column quads per lane that a sweep block lists
 constexpr int kMinSweepBlocks = 4096;  // replicas are split below this many blocks
+constexpr int kMinLightBlocks = 512;   // the same for the short items of a small launch: chunks ...
+constexpr int kMinLightSplit = 768;    // ... and replicas
 constexpr int64_t kMinSweepQuads = 64;  // narrowest column chunk of a sweep block (quads)
 constexpr int64_t kMinGenQuads = 16;    // the same for the generic kernel's one-wave blocks
 constexpr int kCountQuadsPerLane = 8;  // adjacent columns (state quads) per lane and iteration of a count block
@@ -488,13 +529,16 @@ __device__ __forceinline__ void decode_block(uint32_t b, uint32_t count, uint32_
 }
 
 __device__ __forceinline__ Work block_work(const SweepParams &P) {
+    const bool second = blockIdx.x >= P.block_split;
+    const SweepGeom &G = P.geom[second ? 1 : 0];
     uint32_t local;
     int64_t slab;
-    decode_block(blockIdx.x, (uint32_t)P.count, local, slab);
+    decode_block(blockIdx.x - (second ? P.block_split : 0u), (uint32_t)G.count, local, slab);
     Work w;
-    w.node = as_const(P.order)[P.begin + (int32_t)local];
+    w.node = as_const(P.order)[G.begin + (int32_t)local];
     w.d = as_const(P.desc) + as_const(P.desc_off)[w.node];
-    if (slab >= P.n_slabs) {  // padding block of the last round
+    w.quads = G.quads_per_block;
+    if (slab >= G.n_slabs) {  // padding block of the last round
         w.q0 = w.q1 = 0;
         w.r0 = w.r1 = 0;
         return w;
@@ -502,14 +546,14 @@ __device__ __forceinline__ Work block_work(const SweepParams &P) {
     // consecutive colour launches walk the columns in opposite directions, so
     // that a launch starts on the columns the previous one touched last (still
     // in the memory-side cache)
-    if (P.reverse) slab = P.n_slabs - 1 - slab;
-    const int64_t chunk = slab / P.rsplit;
-    const int rpart = (int)(slab % P.rsplit);
+    if (P.reverse) slab = G.n_slabs - 1 - slab;
+    const int64_t chunk = slab / G.rsplit;
+    const int rpart = (int)(slab % G.rsplit);
     const int64_t nquads = (P.n_cols + 3) >> 2;
-    w.q0 = chunk * P.quads_per_block;
-    w.q1 = w.q0 + P.quads_per_block < nquads ? w.q0 + P.quads_per_block : nquads;
-    w.r0 = rpart * P.reps_per_block;
-    w.r1 = w.r0 + P.reps_per_block < P.m ? w.r0 + P.reps_per_block : P.m;
+    w.q0 = chunk * G.quads_per_block;
+    w.q1 = w.q0 + G.quads_per_block < nquads ? w.q0 + G.quads_per_block : nquads;
+    w.r0 = rpart * G.reps_per_block;
+    w.r1 = w.r0 + G.reps_per_block < P.m ? w.r0 + G.reps_per_block : P.m;
     return w;
 }
 
@@ -567,10 +611,10 @@ constexpr int kItemBatch = 4;  // blanket entries whose state quads are in fligh
 constexpr int kFlatGroups = 4;  // product nodes with this many groups take the flat entry walk
 
 // Adds the N entries (node, mult) at e to the item's packed index: every
-// entry's state quad is loaded before the first is used; slots >= nrep read 0.
+// entry's state quad is loaded before the first is used; slots outside mask read 0.
 template <int N, typename ST>
 __device__ __forceinline__ void item_entries(cint32_t *e, const void *__restrict__ states, int64_t vstride,
-                                             uint32_t qoff, int nrep, uint32_t (&Pk)[2]) {
+                                             uint32_t qoff, const SlotMask &mask, uint32_t (&Pk)[2]) {
     using Q = Quad<ST>;
     typename Q::V v[N];
 #pragma unroll
@@ -579,7 +623,7 @@ __device__ __forceinline__ void item_entries(cint32_t *e, const void *__restrict
     for (int t = 0; t < N; ++t) {
         const uint32_t mult = (uint32_t)e[2 * t + 1];
         uint32_t p[2];
-        Q::split(Q::keep(v[t], nrep), p);
+        Q::split(v[t], mask, p);
         Pk[0] = pk_mad_u16(p[0], mult, Pk[0]);
         Pk[1] = pk_mad_u16(p[1], mult, Pk[1]);
     }
@@ -591,7 +635,7 @@ __device__ __forceinline__ void item_entries(cint32_t *e, const void *__restrict
 // occupancy bound allows).
 template <typename ST>
 __device__ __forceinline__ void item_group(cint32_t *&g, const void *__restrict__ states, int64_t vstride,
-                                           uint32_t qoff, int nrep, uint32_t (&Pk)[2]) {
+                                           uint32_t qoff, const SlotMask &mask, uint32_t (&Pk)[2]) {
     __builtin_amdgcn_sched_barrier(0);
     int n_e = g[0];
     Pk[0] = Pk[1] = (uint32_t)g[1];
@@ -599,10 +643,10 @@ __device__ __forceinline__ void item_group(cint32_t *&g, const void *__restrict_
     g += 2 + 2 * n_e;
     for (; n_e > 0; n_e -= kItemBatch, e += 2 * kItemBatch) {
         switch (n_e < kItemBatch ? n_e : kItemBatch) {
-        case 1: item_entries<1, ST>(e, states, vstride, qoff, nrep, Pk); break;
-        case 2: item_entries<2, ST>(e, states, vstride, qoff, nrep, Pk); break;
-        case 3: item_entries<3, ST>(e, states, vstride, qoff, nrep, Pk); break;
-        default: item_entries<4, ST>(e, states, vstride, qoff, nrep, Pk); break;
+        case 1: item_entries<1, ST>(e, states, vstride, qoff, mask, Pk); break;
+        case 2: item_entries<2, ST>(e, states, vstride, qoff, mask, Pk); break;
+        case 3: item_entries<3, ST>(e, states, vstride, qoff, mask, Pk); break;
+        default: item_entries<4, ST>(e, states, vstride, qoff, mask, Pk); break;
         }
     }
 }
@@ -633,9 +677,9 @@ __device__ __forceinline__ void item_multiply(lds_char *lds, global_char *gtab, 
 template <int KP, typename ST, bool STAGED, bool RESCALE>
 __device__ __forceinline__ void item_product(cint32_t *g, int n_groups, int n_staged, lds_char *lds,
                                              global_char *gtab, const void *__restrict__ states, int64_t vstride,
-                                             uint32_t qoff, int nrep, float (&w)[4][KP]) {
+                                             uint32_t qoff, const SlotMask &mask, float (&w)[4][KP]) {
     uint32_t Pk[2];
-    item_group<ST>(g, states, vstride, qoff, nrep, Pk);
+    item_group<ST>(g, states, vstride, qoff, mask, Pk);
     if (STAGED && n_staged > 0) item_multiply<KP, ST, true, RESCALE, true>(lds, gtab, Pk, w);
     else item_multiply<KP, ST, false, RESCALE, true>(lds, gtab, Pk, w);
     // the staged groups, then the global ones: two loops, so that each keeps
@@ -643,12 +687,12 @@ __device__ __forceinline__ void item_product(cint32_t *g, int n_groups, int n_st
     int j = 1;
     if (STAGED) {
         for (; j < n_staged; ++j) {
-            item_group<ST>(g, states, vstride, qoff, nrep, Pk);
+            item_group<ST>(g, states, vstride, qoff, mask, Pk);
             item_multiply<KP, ST, true, RESCALE>(lds, gtab, Pk, w);
         }
     }
     for (; j < n_groups; ++j) {
-        item_group<ST>(g, states, vstride, qoff, nrep, Pk);
+        item_group<ST>(g, states, vstride, qoff, mask, Pk);
         item_multiply<KP, ST, false, RESCALE>(lds, gtab, Pk, w);
     }
 }
@@ -670,7 +714,7 @@ __device__ __forceinline__ void flat_loads(cint32_t *e, const void *__restrict__
 template <int KP, typename ST, bool FROM_LDS>
 __device__ __forceinline__ void item_product_flat(cint32_t *f, lds_char *lds, global_char *gtab,
                                                   const void *__restrict__ states, int64_t vstride, uint32_t qoff,
-                                                  int nrep, float (&w)[4][KP]) {
+                                                  const SlotMask &mask, float (&w)[4][KP]) {
     using Q = Quad<ST>;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -703,7 +747,7 @@ __device__ __forceinline__ void item_product_flat(cint32_t *f, lds_char *lds, gl
             const int flags = x[3];
             if (flags & 1) Pk[0] = Pk[1] = (uint32_t)x[2];
             uint32_t p[2];
-            Q::split(Q::keep(v[s], nrep), p);
+            Q::split(v[s], mask, p);
             Pk[0] = pk_mad_u16(p[0], (uint32_t)x[1], Pk[0]);
             Pk[1] = pk_mad_u16(p[1], (uint32_t)x[1], Pk[1]);
             if (flags & 2) item_multiply<KP, ST, FROM_LDS, false>(lds, gtab, Pk, w);
@@ -711,87 +755,205 @@ __device__ __forceinline__ void item_product_flat(cint32_t *f, lds_char *lds, gl
     }
 }
 
+// The product over a two-state node's group records (E entries each, every
+// k-vector in LDS), kRecordLoads / E groups at a time: their state quads are
+// in flight together, and the next groups' while these are multiplied; then
+// all their k-vectors are read, then multiplied in list order.  The weights
+// start at one (exact).  Nothing depends on an entry's flags, so a batch is
+// straight-line code.  (The flat walk below waits for a scalar load and
+// branches at every entry: about 11 us for the 40 entries of a concept with 20
+// items, when few waves are resident; 6 us so.)
+constexpr int kRecordLoads = 8;
+
+template <typename ST, int E>
+struct RecordBatch {
+    static constexpr int G = kRecordLoads / E;
+    static constexpr int kRecord = (2 * E + 1 + 7) & ~7;  // words
+    typename Quad<ST>::V v[G][E];
+
+    // the quads of the first n groups at r
+    __device__ __forceinline__ void load(cint32_t *r, int n, const char *states, int64_t vstride, uint32_t qoff) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g >= n) break;  // uniform
+#pragma unroll
+            for (int t = 0; t < E; ++t)
+                v[g][t] = Quad<ST>::load_global(
+                    scalar_global_ptr(states + (uint64_t)(uint32_t)r[g * kRecord + 2 * t] * (uint32_t)vstride), qoff);
+        }
+    }
+};
+
+template <typename ST, int E>
+__device__ __forceinline__ void item_product_records(cint32_t *r, int n_groups, lds_char *lds, const char *states,
+                                                     int64_t vstride, uint32_t qoff, const SlotMask &mask,
+                                                     float (&w)[4][2]) {
+    using B = RecordBatch<ST, E>;
+    constexpr int G = B::G;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) w[c][0] = w[c][1] = 1.f;
+    B next;
+    next.load(r, n_groups < G ? n_groups : G, states, vstride, qoff);
+    for (; n_groups > 0; n_groups -= G, r += G * B::kRecord) {
+        const int n = n_groups < G ? n_groups : G, n2 = n_groups - G < G ? n_groups - G : G;
+        const B cur = next;
+        next.load(r + G * B::kRecord, n2, states, vstride, qoff);
+        float f[G][4][2];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g >= n) break;  // uniform
+            uint32_t Pk[2];
+            Pk[0] = Pk[1] = (uint32_t)r[g * B::kRecord + 2 * E];
+#pragma unroll
+            for (int t = 0; t < E; ++t) {
+                const uint32_t mult = (uint32_t)r[g * B::kRecord + 2 * t + 1];
+                uint32_t p[2];
+                Quad<ST>::split(cur.v[g][t], mask, p);
+                Pk[0] = pk_mad_u16(p[0], mult, Pk[0]);
+                Pk[1] = pk_mad_u16(p[1], mult, Pk[1]);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) read_kvec_lds<2>(lds + packed_index<ST>(Pk, c), f[g][c]);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g >= n) break;  // uniform
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                w[c][0] *= f[g][c][0];
+                w[c][1] *= f[g][c][1];
+            }
+        }
+    }
+}
+
 // ------------------------------------------------- latent columns of a block
 //
 // A sweep block lists the latent columns of its chunk in LDS before drawing:
-// lane l reads the obs word of columns c0 + 4l .. c0 + 4l + 3, and a
-// block-wide prefix sum (wave ballots, then the waves' totals) places them.
+// in pass p, lane l reads the obs word of column quad p * BLOCK + l of the
+// chunk, and a block-wide prefix sum (wave ballots, then the waves' totals)
+// places its latent columns.  passes (uniform) <= PASSES.
+template <int PASSES>
 struct LatentLanes {
-    int lat;  // the lane's latent mask
-    int pre;  // latent columns of the wave's lower lanes
+    int lat[PASSES];  // the lane's latent mask
+    int pre[PASSES];  // latent columns of the wave's lower lanes
 };
 
-// The lane's part; the waves' totals go to wave_n (LDS).  The caller
-// synchronises before latent_list.
-template <int BLOCK>
-__device__ __forceinline__ void latent_count(const SweepParams &P, const Work &W, LatentLanes &L,
-                                             int32_t *wave_n) {
-    const int64_t col = 4 * (W.q0 + (int64_t)threadIdx.x);
-    L.lat = col < W.q1 * 4 ? latent_bits(P, W.node, col) : 0;
-    const int cnt = __builtin_popcount(L.lat);
-    const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
+// The lane's part; the waves' totals go to wave_n (LDS, PASSES * BLOCK / 64
+// words).  The caller synchronises before latent_list.
+template <int BLOCK, int PASSES>
+__device__ __forceinline__ void latent_count(const SweepParams &P, const Work &W, LatentLanes<PASSES> &L,
+                                             int32_t *wave_n, int passes = PASSES) {
     auto below = [](uint64_t b) {  // set lanes below this one
         return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
     };
-    L.pre = below(b0) + 2 * below(b1) + 4 * below(b2);
-    if ((threadIdx.x & 63) == 0)
-        wave_n[threadIdx.x >> 6] =
-            __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1) + 4 * __builtin_popcountll(b2);
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        if (p >= passes) break;
+        const int64_t q = W.q0 + p * BLOCK + (int64_t)threadIdx.x;
+        L.lat[p] = q < W.q1 ? latent_bits(P, W.node, 4 * q) : 0;
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        if (p >= passes) break;
+        const int cnt = __builtin_popcount(L.lat[p]);
+        const uint64_t b0 = __ballot(cnt & 1), b1 = __ballot(cnt & 2), b2 = __ballot(cnt & 4);
+        L.pre[p] = below(b0) + 2 * below(b1) + 4 * below(b2);
+        if ((threadIdx.x & 63) == 0)
+            wave_n[p * (BLOCK / 64) + (threadIdx.x >> 6)] =
+                __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1) + 4 * __builtin_popcountll(b2);
+    }
 }
 
-// Lists the columns as offsets from c0 (ascending) and returns their number;
-// the caller synchronises before reading the list.
-template <int BLOCK>
-__device__ __forceinline__ int latent_list(const LatentLanes &L, const int32_t *wave_n, uint16_t *lcol) {
+// Lists the columns as offsets from the chunk's first (ascending) and returns
+// their number; the caller synchronises before reading the list.
+template <int BLOCK, int PASSES>
+__device__ __forceinline__ int latent_list(const LatentLanes<PASSES> &L, const int32_t *wave_n, uint16_t *lcol,
+                                           int passes = PASSES) {
     const int wave = threadIdx.x >> 6;
-    int base = 0, ncl = 0;
+    int ncl = 0;
 #pragma unroll
-    for (int v = 0; v < BLOCK / 64; ++v) {
-        const int nv = wave_n[v];
-        base += v < wave ? nv : 0;
-        ncl += nv;
+    for (int p = 0; p < PASSES; ++p) {
+        if (p >= passes) break;
+        int pos = ncl + L.pre[p];
+#pragma unroll
+        for (int v = 0; v < BLOCK / 64; ++v) {
+            const int nv = wave_n[p * (BLOCK / 64) + v];
+            pos += v < wave ? nv : 0;
+            ncl += nv;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if ((L.lat[p] >> c) & 1) lcol[pos++] = (uint16_t)(4 * (p * BLOCK + threadIdx.x) + c);
     }
-    int pos = base + L.pre;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        if ((L.lat >> c) & 1) lcol[pos++] = (uint16_t)(4 * threadIdx.x + c);
     return ncl;
 }
 
-// The block's latent columns and its replica range, as items.
+// The block's latent columns and its replica range, as items: item t is
+// column t mod ncl of the list and the (t / ncl)-th replica quad of the range
+// (whole quads: ranges start on a quad).  A lane takes every BLOCK-th item.
 struct Items {
     const uint16_t *col;  // latent columns of the chunk, as offsets from c0 (LDS)
-    int64_t c0;
-    int ncl, nrq, r0, r1;
+    uint32_t c0;
+    int ncl, q0, nrq, r1;
     float inv;            // 1 / ncl
 };
 
 __device__ __forceinline__ Items block_items(const Work &W, const uint16_t *lcol, int ncl) {
     Items I;
     I.col = lcol;
-    I.c0 = W.q0 * 4;
+    I.c0 = (uint32_t)(W.q0 * 4);
     I.ncl = ncl;
-    I.r0 = W.r0;
-    I.r1 = W.r1;
+    I.q0 = W.r0 >> 2;
     I.nrq = (W.r1 - W.r0 + 3) >> 2;
+    I.r1 = W.r1;
     I.inv = 1.f / (float)ncl;
     return I;
 }
 
-// Item t -> (column j, first replica rb, replicas nrep).
-__device__ __forceinline__ void item_of(const Items &I, int t, int64_t &j, int &rb, int &nrep) {
-    int rq = (int)((float)t * I.inv);  // t, ncl < 2^24: off by at most one
-    int k = t - rq * I.ncl;
-    if (k < 0) {
-        --rq;
-        k += I.ncl;
-    } else if (k >= I.ncl) {
-        ++rq;
-        k -= I.ncl;
+template <int BLOCK>
+struct ItemIter {
+    int k, rq;  // index in the column list, replica quad of the range
+
+    __device__ ItemIter(const Items &I, int t) : k(t), rq(0) {
+        if (I.ncl < BLOCK) split(I);
     }
-    j = I.c0 + I.col[k];
-    rb = I.r0 + 4 * rq;
-    nrep = I.r1 - rb < 4 ? I.r1 - rb : 4;
+    __device__ bool more(const Items &I) const { return rq < I.nrq; }
+    __device__ void next(const Items &I) {
+        k += BLOCK;
+        if (I.ncl >= BLOCK) {  // uniform: at most one quad further
+            const bool wrap = k >= I.ncl;
+            k = wrap ? k - I.ncl : k;
+            rq = wrap ? rq + 1 : rq;
+        } else {
+            split(I);
+        }
+    }
+    __device__ void split(const Items &I) {  // k, ncl < 2^24: the quotient is off by at most one
+        int q = (int)((float)k * I.inv);
+        k -= q * I.ncl;
+        if (k < 0) {
+            --q;
+            k += I.ncl;
+        } else if (k >= I.ncl) {
+            ++q;
+            k -= I.ncl;
+        }
+        rq += q;
+    }
+    __device__ uint32_t column(const Items &I) const { return I.c0 + I.col[k]; }
+    __device__ int quad(const Items &I) const { return I.q0 + rq; }
+    // real replicas of the quad
+    __device__ int reps(const Items &I) const {
+        const int left = I.r1 - 4 * (I.q0 + rq);
+        return left < 4 ? left : 4;
+    }
+};
+
+// Byte offset of quad q at column j in a node's block (under 2^31 bytes).
+template <typename ST>
+__device__ __forceinline__ uint32_t item_boff(const SweepParams &P, int q, uint32_t j) {
+    return ((uint32_t)q * (uint32_t)P.ld + j) * (uint32_t)Quad<ST>::kBytes;
 }
 
 // Product path (classes 0 and 1, KP <= 8): the block's items, one per lane
@@ -805,21 +967,25 @@ __device__ __forceinline__ void sweep_product(const SweepParams &P, const Work &
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
-    const int n_items = I.ncl * I.nrq;
-    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
-        int64_t j;
-        int rb, nrep;
-        item_of(I, t, j, rb, nrep);
-        const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
+    for (ItemIter<kSweepBlock> it(I, threadIdx.x); it.more(I); it.next(I)) {
+        const uint32_t j = it.column(I);
+        const int rq = it.quad(I), nrep = it.reps(I);
+        const uint32_t qoff = item_boff<ST>(P, rq, j);
+        const SlotMask mask = slot_mask<ST>(nrep);
         float w[4][KP];
         // nodes with many groups (all from LDS, or all from global memory)
         // walk their flat entry list: fewer dependent loads per item
-        if (n_groups < kFlatGroups || (STAGED && n_staged != n_groups))
-            item_product<KP, ST, STAGED, false>(grp, n_groups, n_staged, lds, gtab, states, vstride, qoff, nrep, w);
+        if (STAGED && KP == 2 && d[7] != 0) {
+            if constexpr (STAGED && KP == 2) {
+                if (d[7] == 2) item_product_records<ST, 2>(d + d[6], n_groups, lds, states, vstride, qoff, mask, w);
+                else item_product_records<ST, 4>(d + d[6], n_groups, lds, states, vstride, qoff, mask, w);
+            }
+        } else if (n_groups < kFlatGroups || (STAGED && n_staged != n_groups))
+            item_product<KP, ST, STAGED, false>(grp, n_groups, n_staged, lds, gtab, states, vstride, qoff, mask, w);
         else if (!STAGED)
-            item_product_flat<KP, ST, false>(d + d[15], lds, gtab, states, vstride, qoff, nrep, w);
+            item_product_flat<KP, ST, false>(d + d[15], lds, gtab, states, vstride, qoff, mask, w);
         else
-            item_product_flat<KP, ST, true>(d + d[15], lds, gtab, states, vstride, qoff, nrep, w);
+            item_product_flat<KP, ST, true>(d + d[15], lds, gtab, states, vstride, qoff, mask, w);
         float wd[4][KP];
         if (DEBUG) {
 #pragma unroll
@@ -834,7 +1000,7 @@ __device__ __forceinline__ void sweep_product(const SweepParams &P, const Work &
             low |= c < nrep && !(w[c][KP - 1] >= kUnderflowZ);
         }
         if (low) {
-            item_product<KP, ST, STAGED, true>(grp, n_groups, n_staged, lds, gtab, states, vstride, qoff, nrep, w);
+            item_product<KP, ST, STAGED, true>(grp, n_groups, n_staged, lds, gtab, states, vstride, qoff, mask, w);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if (DEBUG) {
@@ -844,12 +1010,12 @@ __device__ __forceinline__ void sweep_product(const SweepParams &P, const Work &
                 running_sums<KP>(w[c]);
             }
         }
-        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
+        const Philox4 rnd = gibbs_block(P, W.node, rq, j);
         typename Quad<ST>::V out{};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             out = Quad<ST>::put(out, c, draw_sums<KP>(w[c], K, uniform24(rnd.w[c])));
-            if (DEBUG && c < nrep) write_probs(P, W.node, rb + c, j, wd[c], K, w[c][KP - 1]);
+            if (DEBUG && c < nrep) write_probs(P, W.node, 4 * rq + c, j, wd[c], K, w[c][KP - 1]);
         }
         Quad<ST>::store_buffer(own, qoff, out);
     }
@@ -943,13 +1109,16 @@ __device__ __forceinline__ typename Quad<ST>::V table_draws(bool tab_lds, lds_ch
     typename Quad<ST>::V out{};
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const uint32_t u24 = rnd.w[c] >> 8;
+        const uint32_t u1 = (rnd.w[c] >> 8) + 1;  // T <= u24: T - u1 is negative (both at most 2^24)
         uint32_t th[KT];
         read_thresholds<KT>(tab_lds, lds, gcond, packed_index<ST>(Pk, c), th);
-        int pick = 0;
+        uint32_t at_or_below = KT == 1 ? (th[0] - u1) >> 31 : 0u;
+        if (KT > 1) {
 #pragma unroll
-        for (int k = 0; k < KT; ++k) pick += th[k] <= u24 ? 1 : 0;
-        out = Quad<ST>::put(out, c, pick);
+            for (int k = 0; k < KT; ++k) at_or_below = append_sign(at_or_below, th[k] - u1);
+            at_or_below = (uint32_t)__builtin_popcount(at_or_below);
+        }
+        out = Quad<ST>::put(out, c, (int)at_or_below);
     }
     return out;
 }
@@ -975,21 +1144,20 @@ __device__ __forceinline__ void sweep_table_rows(const SweepParams &P, const Wor
         mult[t] = (uint32_t)grp[3 + 2 * t];
     }
     const uint32_t base = (uint32_t)grp[1];
-    const int n_items = I.ncl * I.nrq;
-    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
-        int64_t j;
-        int rb, nrep;
-        item_of(I, t, j, rb, nrep);
-        const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
+    for (ItemIter<kSweepBlock> it(I, threadIdx.x); it.more(I); it.next(I)) {
+        const uint32_t j = it.column(I);
+        const int rq = it.quad(I), nrep = it.reps(I);
+        const uint32_t qoff = item_boff<ST>(P, rq, j);
+        const SlotMask mask = slot_mask<ST>(nrep);
         typename Q::V v[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = Q::load_global(row[i], qoff);
-        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
+        const Philox4 rnd = gibbs_block(P, W.node, rq, j);
         uint32_t Pk[2] = {base, base};
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             uint32_t p[2];
-            Q::split(Q::keep(v[i], nrep), p);
+            Q::split(v[i], mask, p);
             Pk[0] = pk_mad_u16(p[0], mult[i], Pk[0]);
             Pk[1] = pk_mad_u16(p[1], mult[i], Pk[1]);
         }
@@ -1023,19 +1191,17 @@ __device__ __forceinline__ void sweep_table(const SweepParams &P, const Work &W,
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
-    const int n_items = I.ncl * I.nrq;
-    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
-        int64_t j;
-        int rb, nrep;
-        item_of(I, t, j, rb, nrep);
-        const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
+    for (ItemIter<kSweepBlock> it(I, threadIdx.x); it.more(I); it.next(I)) {
+        const uint32_t j = it.column(I);
+        const int rq = it.quad(I), nrep = it.reps(I);
+        const uint32_t qoff = item_boff<ST>(P, rq, j);
         cint32_t *g = grp;
         uint32_t Pk[2];
-        item_group<ST>(g, states, vstride, qoff, nrep, Pk);
-        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
+        item_group<ST>(g, states, vstride, qoff, slot_mask<ST>(nrep), Pk);
+        const Philox4 rnd = gibbs_block(P, W.node, rq, j);
         Quad<ST>::store_buffer(own, qoff, table_draws<KT, ST>(tab_lds, lds, gcond, Pk, rnd));
         if (DEBUG) {
-            for (int c = 0; c < nrep; ++c) table_debug_prob<ST>(P, W, rb + c, j);
+            for (int c = 0; c < nrep; ++c) table_debug_prob<ST>(P, W, 4 * rq + c, j);
         }
     }
 }
@@ -1054,16 +1220,18 @@ template <typename ST, bool DEBUG, bool STAGED>
 __global__ __launch_bounds__(kSweepBlock, DEBUG ? 1 : kSweepWaves) void sweep_fast_kernel(SweepParams P) {
     if (P.ids) P.sweep_id = P.ids[0];
     extern __shared__ float4 lds4[];
-    __shared__ uint16_t lcol[4 * kSweepBlock];
-    __shared__ int32_t wave_n[kSweepBlock / 64];
+    __shared__ int32_t wave_n[kSweepPasses * kSweepBlock / 64];
+    // the column list follows the staged part of the record
+    uint16_t *lcol = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds4) + P.list_off);
     const Work W = block_work(P);
+    const int passes = (W.quads + kSweepBlock - 1) / kSweepBlock;
     if (W.q0 >= W.q1) return;  // uniform across the block
     cint32_t *d = W.d;
     const int mode = d[2];
     const float *tab = P.table + d[3];
     const uint32_t *cond = P.cond + d[5];
-    LatentLanes L;
-    latent_count<kSweepBlock>(P, W, L, wave_n);
+    LatentLanes<kSweepPasses> L;
+    latent_count<kSweepBlock, kSweepPasses>(P, W, L, wave_n, passes);
     if (STAGED) {
         const float4 *src = reinterpret_cast<const float4 *>(mode == kModeTable ? (const void *)cond
                                                                                 : (const void *)tab);
@@ -1071,7 +1239,7 @@ __global__ __launch_bounds__(kSweepBlock, DEBUG ? 1 : kSweepWaves) void sweep_fa
         for (int i = threadIdx.x; i < len4; i += kSweepBlock) lds4[i] = src[i];
     }
     __syncthreads();
-    const int ncl = latent_list<kSweepBlock>(L, wave_n, lcol);
+    const int ncl = latent_list<kSweepBlock, kSweepPasses>(L, wave_n, lcol, passes);
     __syncthreads();
     if (ncl == 0) return;  // uniform
     const Items I = block_items(W, lcol, ncl);
@@ -1106,12 +1274,10 @@ __device__ void sweep_wide(const SweepParams &P, const Work &W, const Items &I) 
     char *states = reinterpret_cast<char *>(P.states);
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     const __amdgpu_buffer_rsrc_t own = node_rsrc<ST>(states, W.node, vstride);
-    const int n_items = I.ncl * I.nrq;
-    for (int t = threadIdx.x; t < n_items; t += kSweepBlock) {
-        int64_t j;
-        int rb, nrep;
-        item_of(I, t, j, rb, nrep);
-        const uint32_t qoff = quad_boff<ST>(rb >> 2, P.ld, j);
+    for (ItemIter<kSweepBlock> it(I, threadIdx.x); it.more(I); it.next(I)) {
+        const uint32_t j = it.column(I);
+        const int rq = it.quad(I), nrep = it.reps(I);
+        const uint32_t qoff = item_boff<ST>(P, rq, j);
         typename Q::V cur = load_row<ST>(states, W.node, vstride, qoff);
         float w[4][KP];
         wide_product<KP, ST, false>(grp, n_groups, tab, states, vstride, qoff, nrep, w);
@@ -1124,7 +1290,7 @@ __device__ void sweep_wide(const SweepParams &P, const Work &W, const Items &I) 
             low |= c < nrep && !(Z >= kUnderflowZ);
         }
         if (low) wide_product<KP, ST, true>(grp, n_groups, tab, states, vstride, qoff, nrep, w);
-        const Philox4 rnd = gibbs_block(P, W.node, rb >> 2, j);
+        const Philox4 rnd = gibbs_block(P, W.node, rq, j);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if (c >= nrep) continue;
@@ -1132,7 +1298,7 @@ __device__ void sweep_wide(const SweepParams &P, const Work &W, const Items &I) 
                 float Z = 0.f;
 #pragma unroll
                 for (int k = 0; k < KP; ++k) Z += w[c][k];
-                write_probs(P, W.node, rb + c, j, w[c], K, Z);
+                write_probs(P, W.node, 4 * rq + c, j, w[c], K, Z);
             }
             running_sums<KP>(w[c]);
             cur = Q::put(cur, c, draw_sums<KP>(w[c], K, uniform24(rnd.w[c])));
@@ -1148,10 +1314,10 @@ __global__ __launch_bounds__(kSweepBlock) void sweep_wide_kernel(SweepParams P) 
     __shared__ int32_t wave_n[kSweepBlock / 64];
     const Work W = block_work(P);
     if (W.q0 >= W.q1) return;  // uniform across the block
-    LatentLanes L;
-    latent_count<kSweepBlock>(P, W, L, wave_n);
+    LatentLanes<1> L;
+    latent_count<kSweepBlock, 1>(P, W, L, wave_n);
     __syncthreads();
-    const int ncl = latent_list<kSweepBlock>(L, wave_n, lcol);
+    const int ncl = latent_list<kSweepBlock, 1>(L, wave_n, lcol);
     __syncthreads();
     if (ncl == 0) return;  // uniform
     const Items I = block_items(W, lcol, ncl);
@@ -1244,10 +1410,10 @@ __global__ __launch_bounds__(kGenBlock) void sweep_generic_kernel(SweepParams P)
     __shared__ __align__(16) GenShared S;
     const Work W = block_work(P);
     if (W.q0 >= W.q1) return;  // uniform across the block
-    LatentLanes L;
-    latent_count<kGenBlock>(P, W, L, wave_n);
+    LatentLanes<1> L;
+    latent_count<kGenBlock, 1>(P, W, L, wave_n);
     __syncthreads();
-    const int ncl = latent_list<kGenBlock>(L, wave_n, lcol);
+    const int ncl = latent_list<kGenBlock, 1>(L, wave_n, lcol);
     __syncthreads();
     if (ncl == 0) return;  // uniform
     cint32_t *d = W.d;
@@ -2623,20 +2789,25 @@ hipError_t launch_build_tables(const DeviceTables &t, const float *cpts, float *
 namespace {
 
 template <typename ST>
-void sweep_class(const SweepParams &P, int32_t klass, int32_t lds_bytes, dim3 grid,
+void sweep_class(SweepParams P, int32_t klass, int32_t lds_bytes, dim3 grid,
                  hipStream_t stream) {
     const bool dbg = P.win > 0;
     const dim3 blk(dev::kSweepBlock);
+    // the fast kernel's LDS: the staged part of a record, then the column list
+    const int32_t quads = P.geom[0].quads_per_block > P.geom[1].quads_per_block ? P.geom[0].quads_per_block
+                                                                                : P.geom[1].quads_per_block;
+    const int32_t list_bytes = quads * 4 * (int32_t)sizeof(uint16_t);
+    P.list_off = klass <= 1 ? lds_bytes : 0;
     if (klass == 0) {
-        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, true>), grid, blk, lds_bytes, stream, P);
-        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, true>), grid, blk, lds_bytes, stream, P);
+        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, true>), grid, blk, lds_bytes + list_bytes, stream, P);
+        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, true>), grid, blk, lds_bytes + list_bytes, stream, P);
     } else if (klass == 1 && lds_bytes > 0) {
         // partially staged records
-        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, true>), grid, blk, lds_bytes, stream, P);
-        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, true>), grid, blk, lds_bytes, stream, P);
+        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, true>), grid, blk, lds_bytes + list_bytes, stream, P);
+        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, true>), grid, blk, lds_bytes + list_bytes, stream, P);
     } else if (klass == 1) {
-        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, false>), grid, blk, 0, stream, P);
-        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, false>), grid, blk, 0, stream, P);
+        if (dbg) hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, true, false>), grid, blk, list_bytes, stream, P);
+        else hipLaunchKernelGGL((dev::sweep_fast_kernel<ST, false, false>), grid, blk, list_bytes, stream, P);
     } else if (klass == 2) {
         if (dbg) hipLaunchKernelGGL((dev::sweep_wide_kernel<ST, true>), grid, blk, 0, stream, P);
         else hipLaunchKernelGGL((dev::sweep_wide_kernel<ST, false>), grid, blk, 0, stream, P);
@@ -2652,43 +2823,75 @@ void sweep_class(const SweepParams &P, int32_t klass, int32_t lds_bytes, dim3 gr
 
 }  // namespace
 
-hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t klass,
+hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_long, int32_t klass,
                         int32_t lds_bytes, int32_t state_bits, hipStream_t stream) {
     if (count <= 0 || P.n_cols <= 0) return hipSuccess;
-    // Slabs of kSweepQuadsPerLane column quads per lane.  A block that stages
-    // its node's table in LDS (class 0) takes all replicas, so that the copy
-    // is paid once per column chunk, and replicas are split only when that
-    // leaves fewer than kMinSweepBlocks blocks; the other classes take one
-    // replica quad per block: smaller slabs keep the blanket rows and the
-    // global tables that the resident blocks gather from in L2 (measured
-    // faster).  A block's replica range is always whole state quads (the
-    // last one ends at m), so that no two blocks write one quad.
     const int64_t quads = (P.n_cols + 3) / 4;
-    P.quads_per_block = klass == 3 ? (int64_t)dev::kGenBlock
-                                   : (int64_t)dev::kSweepBlock * dev::kSweepQuadsPerLane;
-    // the fast kernel draws replicas in quads (one Philox block each), so a
-    // block's replica range is whole quads except at the end
     const int64_t m_quads = (P.m + 3) / 4;
-    // small launches (few nodes or columns) take narrower column chunks, down
-    // to 256 columns (64 for the one-wave blocks of the generic kernel), so
-    // that even with one replica quad per block they fill the device with
-    // blocks
-    const int64_t min_quads = klass == 3 ? dev::kMinGenQuads : dev::kMinSweepQuads;
-    while (P.quads_per_block > min_quads &&
-           count * ((quads + P.quads_per_block - 1) / P.quads_per_block) * m_quads < dev::kMinSweepBlocks)
-        P.quads_per_block /= 2;
-    const int64_t chunks = (quads + P.quads_per_block - 1) / P.quads_per_block;
-    int64_t rsplit = klass == 0 ? (dev::kMinSweepBlocks + count * chunks - 1) / (count * chunks) : m_quads;
-    if (rsplit > m_quads) rsplit = m_quads;
-    if (rsplit < 1) rsplit = 1;
-    const int64_t quads_per_block = (m_quads + rsplit - 1) / rsplit;
-    P.rsplit = (int32_t)((m_quads + quads_per_block - 1) / quads_per_block);
-    P.reps_per_block = (int32_t)(4 * quads_per_block);
-    P.n_slabs = chunks * P.rsplit;
-    P.count = count;
-    P.begin = begin;
-    const int64_t rounds = (P.n_slabs + dev::kXcds - 1) / dev::kXcds;
-    const int64_t blocks = rounds * dev::kXcds * count;
+    auto chunks_of = [&](int64_t q) { return (quads + q - 1) / q; };
+    // Nodes [from, from + n) in column chunks of at most `wide` quads,
+    // narrowed down to `narrow` while the launch has fewer than min_blocks
+    // blocks even with one replica quad per block.  A block that stages its
+    // node's table in LDS (class 0) takes all replicas, so that the copy is
+    // paid once per column chunk, and replicas are split only when that leaves
+    // fewer than split_blocks blocks; the other classes take one replica quad
+    // per block: smaller slabs keep the blanket rows and the global tables
+    // that the resident blocks gather from in L2 (measured faster).  A block's
+    // replica range is always whole state quads (the last one ends at m), so
+    // that no two blocks write one quad.
+    auto geometry = [&](int32_t from, int32_t n, int64_t wide, int64_t narrow, int64_t min_blocks,
+                        int64_t split_blocks) {
+        SweepGeom G{};
+        int64_t q = wide;
+        while (q > narrow && n * chunks_of(q) * m_quads < min_blocks) q /= 2;
+        const int64_t chunks = chunks_of(q);
+        int64_t rsplit = klass == 0 && n > 0 ? (split_blocks + n * chunks - 1) / (n * chunks) : m_quads;
+        if (rsplit > m_quads) rsplit = m_quads;
+        if (rsplit < 1) rsplit = 1;
+        const int64_t rq = (m_quads + rsplit - 1) / rsplit;
+        G.begin = from;
+        G.count = n;
+        G.quads_per_block = (int32_t)q;
+        G.rsplit = (int32_t)((m_quads + rq - 1) / rq);
+        G.reps_per_block = (int32_t)(4 * rq);
+        G.n_slabs = chunks * G.rsplit;
+        return G;
+    };
+    const int64_t block_quads = klass == 3 ? dev::kGenBlock : dev::kSweepBlock;
+    const bool small = count * chunks_of(block_quads) * m_quads < dev::kMinSweepBlocks;
+    int n_geom = 1;
+    if (klass == 0 && small) {
+        // a small launch: long items in the narrowest chunks that fill the
+        // device, the others in wide ones.  A block of one short item per
+        // lane is nearly all start; one of several long ones per lane is the
+        // launch's tail.  Six launches of 30 concepts (20 groups) and 300
+        // items over 4000 columns, m = 20: 17-21 us each with every node in
+        // 256-column chunks (1024-column chunks: over 50), 11-13 us so.
+        if (n_long > 0) P.geom[0] = geometry(begin, n_long, block_quads, dev::kMinSweepQuads, dev::kMinSweepBlocks,
+                                                 dev::kMinSweepBlocks);
+        if (n_long < count)
+            P.geom[n_long > 0 ? 1 : 0] =
+                geometry(begin + n_long, count - n_long, block_quads, dev::kMinSweepQuads, dev::kMinLightBlocks,
+                         dev::kMinLightSplit);
+        n_geom = n_long > 0 && n_long < count ? 2 : 1;
+    } else {
+        // of few replica quads a block takes more columns, so that its lanes
+        // have as many items and a column slab of a row as many bytes: 100
+        // nodes x 1M columns, m = 5, 837 -> 805 us per step with 2048
+        // columns; three quads keep 1024 (1000-node network 4.76 ms, 5.14 with
+        // 2048: the slab's rows no longer stay in L2)
+        const int64_t wide = klass != 0 ? block_quads : block_quads * (m_quads <= 1 ? 4 : m_quads == 2 ? 2 : 1);
+        P.geom[0] = geometry(begin, count, wide, klass == 3 ? dev::kMinGenQuads : dev::kMinSweepQuads,
+                             dev::kMinSweepBlocks, dev::kMinSweepBlocks);
+    }
+    // whole rounds of blocks over the XCDs, so that the second part's blocks
+    // start on the first XCD
+    int64_t blocks = 0;
+    P.block_split = 0xffffffffu;
+    for (int g = 0; g < n_geom; ++g) {
+        if (g == 1) P.block_split = (uint32_t)blocks;
+        blocks += (P.geom[g].n_slabs + dev::kXcds - 1) / dev::kXcds * dev::kXcds * P.geom[g].count;
+    }
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     by_format(state_bits, [&](auto tag) { sweep_class<decltype(tag)>(P, klass, lds_bytes, grid, stream); });

@@ -35,12 +35,20 @@ struct DeviceTables {
     int32_t n_cond_blocks = 0;
 };
 
+// `count` nodes from order[begin] on, times n_slabs slabs (a column chunk of
+// quads_per_block column quads x one of rsplit replica ranges of
+// reps_per_block).
+struct SweepGeom {
+    int64_t n_slabs;
+    int32_t begin, count;
+    int32_t quads_per_block, rsplit, reps_per_block;
+};
+
 // Kernel arguments of the sweep (passed by value).
 struct SweepParams {
     const int32_t *desc;
     const int32_t *desc_off;
     const int32_t *order;
-    int32_t begin;                 // first entry of order[] in this launch
     const float *table;            // regrouped k-vector tables (workspace)
     const uint32_t *cond;          // threshold tables (workspace)
     void *states;
@@ -48,14 +56,12 @@ struct SweepParams {
     int32_t m;
     int64_t n_cols, ld, col_offset;
     uint32_t key0, key1, sweep_id;
-    // block geometry, set by the launcher: a launch covers `count` nodes x
-    // `n_slabs` slabs (a column chunk of quads_per_block quads x a replica
-    // range of reps_per_block); see block_work in kernels.hip
-    int64_t quads_per_block;
-    int32_t reps_per_block;
-    int32_t count;
-    int32_t rsplit;
-    int64_t n_slabs;
+    // block geometry, set by the launcher: the launch's blocks are those of
+    // geom[0], then (from block_split on) those of geom[1]; see block_work in
+    // kernels.hip
+    SweepGeom geom[2];
+    uint32_t block_split;
+    int32_t list_off;              // fast kernel: byte offset of the column list in dynamic LDS
     int64_t win_begin, win;        // debug window (win == 0: none)
     int32_t reverse;               // 1: slabs in descending order (see block_work)
     float *probs;
@@ -76,10 +82,11 @@ hipError_t launch_build_thresholds(const DeviceTables &t, const float *cpts, uin
 hipError_t launch_prepare(const DeviceTables &t, const float *cpts, float *table, uint32_t *cond, int32_t *zero,
                           int64_t zero_count, hipStream_t stream);
 
-// Nodes order[begin .. begin+count) of one colour, all of launch class klass
+// Nodes order[begin .. begin+count) of one colour, the first n_long of them
+// with long items (kLongItem), all of launch class klass
 // (0: fast kernel, tables staged in lds_bytes of LDS; 1: fast kernel, tables
 // in global memory; 2: wide kernel; 3: generic kernel).
-hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t klass,
+hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_long, int32_t klass,
                         int32_t lds_bytes, int32_t state_bits, hipStream_t stream);
 
 hipError_t launch_fill_zero(int32_t *p, int64_t count, hipStream_t stream);

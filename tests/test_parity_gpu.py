@@ -226,6 +226,42 @@ def test_many_group_nodes(bits, lds):
     _custom_case(net, st, ob, th, 6, 1000, win=(0, 64), table_limit=0, **kw)
 
 
+@pytest.mark.parametrize("n_kids,n_par", [(4, 0), (5, 1), (8, 1), (9, 2), (7, 3), (12, 4)])
+@pytest.mark.parametrize("bits", [0, 4, 16])
+def test_group_records(n_kids, n_par, bits):
+    """Two-state product nodes with fixed-size group records: 4, 8 and 9 groups
+    after the root's own (batches of four with a rest), groups of at most two
+    entries and of up to four (an own row of three or four parents: batches of
+    two), and an own row of five parents, which has none."""
+    par = list(range(n_par))
+    hub = n_par                     # the node under test
+    parents = [[] for _ in par] + [par]
+    for k in range(n_kids):         # children with the hub and at most one parent more
+        parents.append([hub] if k % 2 or not par else [par[k % n_par], hub])
+    parents.append(par + [hub] if n_par == 4 else [hub])
+    card = [2] * len(parents)
+    if bits == 16:
+        parents, card = parents + [[]], card + [130]
+    net, st, ob, th = _custom(parents, card, 777, 6, 0.5, 7 * n_kids + n_par)
+    _custom_case(net, st, ob, th, 6, 777, win=(0, 64), table_limit=0, **(dict(state_bits=4) if bits == 4 else {}))
+
+
+@pytest.mark.parametrize("n_cols,m", [(70_000, 3), (70_000, 6), (4_099, 2), (150_003, 1)])
+def test_wide_chunks(n_cols, m):
+    """Blocks that list up to four column quads per lane (one replica quad),
+    two (two quads) and one, in launches of 4096 blocks and more, and a small
+    launch whose long and short items take different chunks."""
+    rng = np.random.default_rng(m)
+    parents = [[] for _ in range(40)] + [[int(p) for p in sorted(rng.choice(40, 2, replace=False))] for _ in range(80)]
+    net, st, ob, th = _custom(parents, [2] * 120, n_cols, m, 0.3, 5)
+    ctx = H.context_for(net)
+    color = oracle.graph(net.parents, net.card)["color"]
+    gpu, _ = H.gpu_sweep(ctx, st, ob, th, m, n_cols, 0, 5, 1)
+    ref = st.copy()
+    res = oracle.sweep(net.parents, net.card, th, color, ref, ob, m, n_cols, 0, 5, 1, want_flags=True)
+    H.compare_states(gpu, ref, res["flags"], color, n_cols, obs=ob)
+
+
 def test_zero_columns_is_noop():
     net, st, ob, th = _custom([[], [0]], [2, 2], 8, 2, 0.5, 1, ld=8)
     ctx = H.context_for(net)
