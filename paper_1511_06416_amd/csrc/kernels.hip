@@ -1830,13 +1830,17 @@ struct Span {
     // The span's NQ x 4 states as 16-bit lanes, 2 NQ words: for 8- and
     // 16-bit states two slots of one column per word (Quad::split); for 4-bit
     // states one slot of two adjacent columns per word (a 32-bit word holds
-    // the quads of columns 2p and 2p + 1, so one shift and mask per slot).
+    // the quads of columns 2p and 2p + 1, so one shift and mask per slot, and
+    // for the top slot a shift of both halves alone).
     __device__ void lanes(uint32_t (&L)[2 * NQ]) const {
         if constexpr (Quad<ST>::kBytes == 2) {
 #pragma unroll
-            for (int p = 0; p < NQ / 2; ++p)
+            for (int p = 0; p < NQ / 2; ++p) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) L[4 * p + c] = (w[p] >> (4 * c)) & 0x000f000fu;
+                for (int c = 0; c < 3; ++c) L[4 * p + c] = (w[p] >> (4 * c)) & 0x000f000fu;
+                L[4 * p + 3] = __builtin_bit_cast(
+                    uint32_t, (u16x2)(__builtin_bit_cast(u16x2, w[p]) >> (unsigned short)12));
+            }
         } else {
 #pragma unroll
             for (int h = 0; h < NQ; ++h) {
@@ -1949,14 +1953,17 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
         return;
     }
     // packed 16-bit bins.  The histogram mode is uniform per block, so each
-    // mode has its own copy of the column loop: no per-slot dispatch.
+    // mode has its own copy of the column loop: no per-slot dispatch.  In the
+    // modes of one LDS histogram the index is formed in bytes of LDS (with the
+    // lane's copy), so that a slot costs its extraction and the atomic.
     auto run = [&](auto md) {
         constexpr int MD = decltype(md)::value;
+        constexpr uint32_t kScale = MD == 0 ? 4 * kCopies : MD == 1 ? 4 : 1;
+        static_assert(4 * kCopies * kRepBins <= 65536 && 4 * kLdsBins <= 65536, "byte indices in 16 bits");
+        const uint32_t base = MD == 0 ? (uint32_t)(4 * copy) * 0x10001u : 0u;
         auto add = [&](uint32_t bin) {
-            if constexpr (MD == 0) {
-                atomicAdd(&hist[bin * kCopies + copy], 1);
-            } else if constexpr (MD == 1) {
-                atomicAdd(&hist[bin], 1);
+            if constexpr (MD == 0 || MD == 1) {
+                atomicAdd(reinterpret_cast<int32_t *>(reinterpret_cast<char *>(hist) + bin), 1);
             } else if constexpr (MD == 3) {
                 const uint32_t hb = bin - (uint32_t)lo;
                 if (hb < (uint32_t)range) atomicAdd(&hist[hb], 1);
@@ -1969,33 +1976,34 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
             const bool whole = col + NQ <= ld;
             // every lane of the wave holds NQ columns (uniform)
             const bool full = __all(nvalid == NQ);
-            for (int rq0 = qb; rq0 < qe; rq0 += kCountQuads) {
-                const int nq = qe - rq0 < kCountQuads ? qe - rq0 : kCountQuads;
-                uint32_t boff[kCountQuads];
-                S own[kCountQuads];
-                // every slot loads (a fixed count keeps all loads in flight at
-                // once); slots past the last replica quad read through the
-                // node's buffer resource past its end, which returns 0 without
-                // a memory access, and their values are never used
+            // NT replica quads from rq0 on: a fixed number, so that the code is
+            // straight and all their loads are in flight together
+            auto quads = [&](auto nt, int rq0) {
+                constexpr int NT = decltype(nt)::value;
+                uint32_t boff[NT];
+                S own[NT];
 #pragma unroll
-                for (int t = 0; t < kCountQuads; ++t) {
+                for (int t = 0; t < NT; ++t) {
                     boff[t] = quad_boff<ST>(rq0 + t, ld, col);
                     own[t].template load<WIDE>(states, node, vstride, boff[t], whole);
                 }
                 // bin = sum over parents of x_p * (stride_p * K) + x_node
-                uint32_t Pk[kCountQuads][2 * NQ];
+                uint32_t Pk[NT][2 * NQ];
 #pragma unroll
-                for (int t = 0; t < kCountQuads; ++t) own[t].lanes(Pk[t]);
+                for (int t = 0; t < NT; ++t) {
+                    own[t].lanes(Pk[t]);
+                    if (kScale != 1)
+#pragma unroll
+                        for (int i = 0; i < 2 * NQ; ++i) Pk[t][i] = pk_mad_u16(Pk[t][i], kScale * 0x10001u, base);
+                }
                 for (int q = 0; q < n_par; ++q) {
-                    const uint32_t mult = (uint32_t)(par[2 * q + 1] * K) * 0x10001u;
-                    S sp[kCountQuads];
+                    const uint32_t mult = (uint32_t)(par[2 * q + 1] * K) * kScale * 0x10001u;
+                    S sp[NT];
 #pragma unroll
-                    for (int t = 0; t < kCountQuads; ++t)
+                    for (int t = 0; t < NT; ++t)
                         sp[t].template load<WIDE>(states, par[2 * q], vstride, boff[t], whole);
-                    // slots past the last quad compute on zeros and are never
-                    // counted: no exit from the unrolled loop
 #pragma unroll
-                    for (int t = 0; t < kCountQuads; ++t) {
+                    for (int t = 0; t < NT; ++t) {
                         uint32_t L[2 * NQ];
                         sp[t].lanes(L);
 #pragma unroll
@@ -2003,8 +2011,7 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < kCountQuads; ++t) {
-                    if (t >= nq) continue;  // uniform
+                for (int t = 0; t < NT; ++t) {
                     const int nrep = m - 4 * (rq0 + t) < 4 ? m - 4 * (rq0 + t) : 4;
                     if (full) {
                         // uniform branches only
@@ -2022,7 +2029,11 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
                                     if (h < nvalid) add(S::lane_of(Pk[t], h, c));
                     }
                 }
-            }
+            };
+            int rq = qb;
+            for (; rq + kCountQuads <= qe; rq += kCountQuads) quads(std::integral_constant<int, kCountQuads>{}, rq);
+            if (qe - rq == 2) quads(std::integral_constant<int, 2>{}, rq);
+            else if (qe - rq == 1) quads(std::integral_constant<int, 1>{}, rq);
         }
     };
     if (mode == 0) run(std::integral_constant<int, 0>{});
