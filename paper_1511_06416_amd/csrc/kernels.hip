@@ -1874,7 +1874,7 @@ constexpr int kCountQuads = 3;  // replica quads whose rows are loaded together 
 // sweep) when the node has at most 2^16 bins, else with 32-bit indices.
 // Padding slots (replicas >= m) and columns past the slab are not counted.
 template <typename ST, bool WIDE>
-__global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict__ cdesc,
+__global__ __launch_bounds__(kBlock, Quad<ST>::kBytes == 2 ? 5 : Quad<ST>::kBytes == 4 ? 4 : 2) void count_kernel(const int32_t *__restrict__ cdesc,
                                                       const int32_t *__restrict__ cdesc_off,
                                                       const int32_t *__restrict__ cwork,
                                                       int32_t count, int64_t n_slabs,
@@ -1980,6 +1980,7 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
             // straight and all their loads are in flight together
             auto quads = [&](auto nt, int rq0) {
                 constexpr int NT = decltype(nt)::value;
+                constexpr bool kAhead = Quad<ST>::kBytes == 2 || NT < kCountQuads;
                 uint32_t boff[NT];
                 S own[NT];
 #pragma unroll
@@ -1987,6 +1988,13 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
                     boff[t] = quad_boff<ST>(rq0 + t, ld, col);
                     own[t].template load<WIDE>(states, node, vstride, boff[t], whole);
                 }
+                // the first parent's rows with the node's own, each later one's
+                // while its predecessor is added
+                S ahead[NT];
+                if (kAhead && n_par > 0)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        ahead[t].template load<WIDE>(states, par[0], vstride, boff[t], whole);
                 // bin = sum over parents of x_p * (stride_p * K) + x_node
                 uint32_t Pk[NT][2 * NQ];
 #pragma unroll
@@ -2000,8 +2008,14 @@ __global__ __launch_bounds__(kBlock) void count_kernel(const int32_t *__restrict
                     const uint32_t mult = (uint32_t)(par[2 * q + 1] * K) * kScale * 0x10001u;
                     S sp[NT];
 #pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        sp[t].template load<WIDE>(states, par[2 * q], vstride, boff[t], whole);
+                    for (int t = 0; t < NT; ++t) {
+                        if (kAhead) sp[t] = ahead[t];
+                        else sp[t].template load<WIDE>(states, par[2 * q], vstride, boff[t], whole);
+                    }
+                    if (kAhead && q + 1 < n_par)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            ahead[t].template load<WIDE>(states, par[2 * q + 2], vstride, boff[t], whole);
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         uint32_t L[2 * NQ];
