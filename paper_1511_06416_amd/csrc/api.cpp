@@ -310,8 +310,12 @@ int prepare_sweep(same_ctx *ctx, same::DeviceTables *t, void *states, const uint
     return SAME_OK;
 }
 
-// All colour groups over columns [t0, t0 + nt) of the minibatch described by P.
-int sweep_tile(same_ctx *ctx, const same::SweepParams &P0, int64_t t0, int64_t nt, hipStream_t s) {
+// All colour groups over columns [t0, t0 + nt) of the minibatch described by
+// P.  A small network's single launch adds the tile's histograms to counts
+// (nullable), which *counted reports; the others leave the counts to the
+// caller.
+int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepParams &P0, int64_t t0, int64_t nt,
+               hipStream_t s, int32_t *counts = nullptr, bool *counted = nullptr) {
     const same::Compiled &g = ctx->g;
     same::SweepParams P = P0;
     P.states = (char *)P0.states + t0 * g.quad_bytes;  // column t0 of every quad row
@@ -319,6 +323,12 @@ int sweep_tile(same_ctx *ctx, const same::SweepParams &P0, int64_t t0, int64_t n
     P.n_cols = nt;
     P.col_offset = P0.col_offset + t0;
     P.win_begin = P0.win_begin - t0;
+    if (counted) *counted = false;
+    // per-launch timing reports the colour launches
+    if (P.win == 0 && !ctx->timing.on && same::tiny_network(g, P.m)) {
+        if (counted) *counted = counts != nullptr;
+        return check_hip(same::launch_tiny(P, t, g, counts, s), "small-network launch");
+    }
     StreamRes *sr = nullptr;
     int rc = stream_res_for_current_device(ctx, &sr);
     if (rc) return rc;
@@ -417,7 +427,7 @@ int do_sweep(same_ctx *ctx, void *states, const uint8_t *obs, const float *cpts,
     if (rc) return rc;
     const int64_t T = tile_cols(ctx, m, n_cols);
     for (int64_t t0 = 0; t0 < n_cols; t0 += T) {
-        rc = sweep_tile(ctx, P, t0, n_cols - t0 < T ? n_cols - t0 : T, s);
+        rc = sweep_tile(ctx, *t, P, t0, n_cols - t0 < T ? n_cols - t0 : T, s);
         if (rc) return rc;
     }
     return SAME_OK;
@@ -456,8 +466,10 @@ int do_step(same_ctx *ctx, void *states, const uint8_t *obs, float *cpts, int32_
     const int64_t T = tile_cols(ctx, m, n_cols);
     for (int64_t t0 = 0; t0 < n_cols; t0 += T) {
         const int64_t nt = n_cols - t0 < T ? n_cols - t0 : T;
-        rc = sweep_tile(ctx, P, t0, nt, s);
+        bool counted = false;
+        rc = sweep_tile(ctx, *t, P, t0, nt, s, newc, &counted);
         if (rc) return rc;
+        if (counted) continue;
         rc = check_hip(same::launch_counts(*t, states, ctx->g.state_bits, m, t0, nt, ld, newc, s),
                        "count launch");
         if (rc) return rc;

@@ -572,6 +572,10 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
         }
     }
 
+    g.tiny = n <= kTinyNodes && g.off[n] <= kTinyBins && g.cond_words <= kTinyCondWords;
+    for (int32_t i = 0; i < n; ++i)
+        g.tiny = g.tiny && g.mode[i] == kModeTable && g.klass[i] == 0;
+
     // count work ordered by each family's smallest parent (a root by itself,
     // just before the families whose smallest parent it is): families that
     // share a parent run together, so its rows are re-read from L2 rather

@@ -75,6 +75,14 @@ constexpr int32_t kDescHeader = 16;
 // a block's start (lists, staging), so a small launch rather has more blocks
 // than more items per lane
 constexpr int64_t kLongItem = 16;
+// A small network (tiny_step_kernel): every node draws from a staged threshold
+// table, and at most so many nodes, CPT entries (the histogram's 32 copies
+// take 16 KB) and threshold words; a wave's columns of all nodes and replicas
+// take at most kTinyWaveBytes, so that two blocks and more fit a CU.
+constexpr int32_t kTinyNodes = 24;
+constexpr int64_t kTinyBins = 128;
+constexpr int64_t kTinyCondWords = 2048;
+constexpr int64_t kTinyWaveBytes = 8192;
 constexpr int32_t kRecordGroups = 4;         // fewest groups that get records (see the descriptor)
 constexpr int64_t kPackedLimit = 65536;      // packed indices are 16-bit
 constexpr int32_t kCountLdsBins = 8192;      // bins of the count kernel's LDS histogram
@@ -182,6 +190,7 @@ struct Compiled {
     std::vector<int32_t> launch_long;  // [n_colors * kLaunchClasses] leading nodes with long items (kLongItem)
     std::vector<int32_t> mode;         // [n]
     std::vector<int32_t> klass;        // [n] launch class
+    bool tiny = false;                 // a small network (see kTinyNodes)
 
     // CPT rows, for the Dirichlet normalisation: entry offset and K of each row
     std::vector<int32_t> row_off, row_k;

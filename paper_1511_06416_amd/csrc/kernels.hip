@@ -515,6 +515,7 @@ struct Work {
 constexpr uint32_t kXcds = 8;
 constexpr int kSweepPasses = 4;  // most column quads per lane that a sweep block lists
 constexpr int kMinSweepBlocks = 4096;  // replicas are split below this many blocks
+constexpr int kTinyWaves = 2048;       // small networks: waves of a launch before a wave takes more columns
 constexpr int kMinLightBlocks = 512;   // the same for the short items of a small launch: chunks ...
 constexpr int kMinLightSplit = 768;    // ... and replicas
 constexpr int64_t kMinSweepQuads = 64;  // narrowest column chunk of a sweep block (quads)
@@ -2069,6 +2070,167 @@ __global__ __launch_bounds__(kBlock, Quad<ST>::kBytes == 2 ? 5 : Quad<ST>::kByte
     }
 }
 
+// ----------------------------------------------------- small networks
+//
+// A network whose every node draws from a threshold table, small enough for
+// its tables, its histogram and some columns of all its nodes to share one
+// block's LDS, is swept whole in one launch: a wave takes 64 x G columns with
+// all replicas, reads their states and obs once, draws the colours in order in
+// LDS -- the columns of a wave depend on no other wave -- counts from there
+// (COUNT) and writes the latent quads back.  Bound by the start of the launch
+// and a wave's chain of draws; a launch per colour and one for the counts have
+// that start four times for the five-node student network (3 x 4.3 + 4.8 us
+// at 2,000 columns, 3 x 6.7 + 6.5 us at 100,000, m = 10).
+struct TinyLds {  // byte offsets; the rest of a wave's part at wave * wave_bytes
+    int32_t hist, waves, wave_bytes, list, states;  // list, states: inside a wave's part (masks first)
+};
+
+// The draws of one node's items over the wave's columns.
+template <int KT, typename ST>
+__device__ __forceinline__ void tiny_node(const SweepParams &P, cint32_t *d, int node, int ncl, const uint16_t *list,
+                                          char *tile, int cols, uint32_t c0, lds_char *table) {
+    using Q = Quad<ST>;
+    const int mq = (P.m + 3) >> 2, lane = (int)threadIdx.x & 63;
+    const float inv = 1.f / (float)ncl;
+    cint32_t *g = d + d[9];
+    const int n_e = g[0];
+    const uint32_t base = (uint32_t)g[1];
+    const int row = mq * cols * Q::kBytes;  // LDS bytes of one node's columns
+    for (int t = lane; t < ncl * mq; t += 64) {
+        int rq = (int)((float)t * inv), k = t - rq * ncl;  // off by at most one
+        if (k < 0) {
+            --rq;
+            k += ncl;
+        } else if (k >= ncl) {
+            ++rq;
+            k -= ncl;
+        }
+        const int col = list[k], at = (rq * cols + col) * Q::kBytes;
+        const SlotMask mask = slot_mask<ST>(P.m - 4 * rq < 4 ? P.m - 4 * rq : 4);
+        const Philox4 rnd = gibbs_block(P, node, rq, (int64_t)c0 + col);
+        uint32_t Pk[2] = {base, base};
+        for (int e = 0; e < n_e; ++e) {
+            const typename Q::V v = Q::load_at(tile + g[2 + 2 * e] * row + at);
+            uint32_t p[2];
+            Q::split(v, mask, p);
+            Pk[0] = pk_mad_u16(p[0], (uint32_t)g[3 + 2 * e], Pk[0]);
+            Pk[1] = pk_mad_u16(p[1], (uint32_t)g[3 + 2 * e], Pk[1]);
+        }
+        Q::store_at(tile + node * row + at, table_draws<KT, ST>(true, table, nullptr, Pk, rnd));
+    }
+}
+
+template <typename ST, bool COUNT>
+__global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLds O, int32_t n, int32_t groups,
+                                                          int32_t cond_words, int32_t n_bins,
+                                                          const int32_t *__restrict__ cdesc,
+                                                          const int32_t *__restrict__ cdesc_off,
+                                                          int32_t *__restrict__ counts) {
+    using Q = Quad<ST>;
+    if (P.ids) P.sweep_id = P.ids[0];
+    extern __shared__ float4 lds4[];
+    char *lds = reinterpret_cast<char *>(lds4);
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    const int mq = (P.m + 3) >> 2, cols = 64 * groups;
+    char *mine = lds + O.waves + wave * O.wave_bytes;
+    uint64_t *masks = reinterpret_cast<uint64_t *>(mine);  // latent columns, [node][group]
+    uint16_t *list = reinterpret_cast<uint16_t *>(mine + O.list);
+    char *tile = mine + O.states;                          // state quads, [node][mq][cols]
+    int32_t *hist = reinterpret_cast<int32_t *>(lds + O.hist);
+    const int64_t c0 = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * cols;  // the wave's first column
+    for (int i = threadIdx.x; i < cond_words; i += kBlock) reinterpret_cast<uint32_t *>(lds)[i] = P.cond[i];
+    if (COUNT)
+        for (int i = threadIdx.x; i < n_bins * kCopies; i += kBlock) hist[i] = 0;
+    const int64_t vstride = node_bytes<ST>(P.m, P.ld);
+    char *states = reinterpret_cast<char *>(P.states);
+    for (int i = 0; i < n; ++i)
+        for (int g = 0; g < groups; ++g) {
+            const int64_t j = c0 + 64 * g + lane;
+            const bool in = j < P.n_cols;
+            const uint64_t lat = __ballot(in && P.obs[(int64_t)i * P.ld + (in ? j : 0)] == 0);
+            if (lane == 0) masks[i * groups + g] = lat;
+            const char *src = states + (int64_t)i * vstride + quad_boff<ST>(0, P.ld, in ? j : 0);
+            char *dst = tile + ((int64_t)i * mq * cols + 64 * g + lane) * Q::kBytes;
+#pragma unroll 4
+            for (int rq = 0; rq < mq; ++rq) {
+                const typename Q::V v = Q::load_at(src + (int64_t)rq * P.ld * Q::kBytes);
+                if (in) Q::store_at(dst + rq * cols * Q::kBytes, v);
+            }
+        }
+    __syncthreads();
+    if (c0 < P.n_cols) {
+        for (int o = 0; o < n; ++o) {
+            const int node = as_const(P.order)[o];
+            cint32_t *d = as_const(P.desc) + as_const(P.desc_off)[node];
+            int ncl = 0;
+            for (int g = 0; g < groups; ++g) {
+                const uint64_t lat = masks[node * groups + g];
+                if ((lat >> lane) & 1)
+                    list[ncl + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lat >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)lat, 0u))] =
+                        (uint16_t)(64 * g + lane);
+                ncl += __builtin_popcountll(lat);
+            }
+            // the wave's LDS operations stay in program order: the list, then
+            // its reads; a node's draws, then the next colour's reads
+            __builtin_amdgcn_wave_barrier();
+            if (ncl == 0) continue;
+            lds_char *table = (lds_char *)lds4 + 4 * d[5];
+            const int KT = d[7];
+            if (KT == 1) tiny_node<1, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
+            else if (KT == 2) tiny_node<2, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
+            else if (KT == 4) tiny_node<4, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
+            else tiny_node<8, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
+            __builtin_amdgcn_wave_barrier();
+        }
+        const int row = mq * cols * Q::kBytes;
+        for (int i = 0; i < n; ++i) {
+            cint32_t *d = as_const(cdesc) + as_const(cdesc_off)[i];
+            const int K = d[0], n_par = d[1], off = d[3];
+            cint32_t *par = d + 4;
+            for (int g = 0; g < groups; ++g) {
+                const int64_t j = c0 + 64 * g + lane;
+                const bool in = j < P.n_cols;
+                const uint64_t lat = masks[i * groups + g];
+                const bool write = (lat >> lane) & 1;
+                for (int rq = 0; rq < mq; ++rq) {
+                    const int at = (rq * cols + 64 * g + lane) * Q::kBytes;
+                    const typename Q::V own = Q::load_at(tile + i * row + at);
+                    if (write)
+                        Q::store_at(states + (int64_t)i * vstride + quad_boff<ST>(rq, P.ld, j), own);
+                    if constexpr (COUNT) {
+                        // bins in bytes of the lane's histogram copy
+                        uint32_t Pk[2], p[2];
+                        Q::split(own, p);
+                        Pk[0] = pk_mad_u16(p[0], 4 * kCopies * 0x10001u, (uint32_t)(4 * (lane & (kCopies - 1))) * 0x10001u);
+                        Pk[1] = pk_mad_u16(p[1], 4 * kCopies * 0x10001u, (uint32_t)(4 * (lane & (kCopies - 1))) * 0x10001u);
+                        for (int q = 0; q < n_par; ++q) {
+                            const uint32_t mult = (uint32_t)(par[2 * q + 1] * K) * (4 * kCopies) * 0x10001u;
+                            Q::split(Q::load_at(tile + par[2 * q] * row + at), p);
+                            Pk[0] = pk_mad_u16(p[0], mult, Pk[0]);
+                            Pk[1] = pk_mad_u16(p[1], mult, Pk[1]);
+                        }
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (in && 4 * rq + c < P.m)
+                                atomicAdd(reinterpret_cast<int32_t *>(reinterpret_cast<char *>(hist + off * kCopies) +
+                                                                      packed_index<ST>(Pk, c)), 1);
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (COUNT) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < n_bins; b += kBlock) {
+            int v = 0;
+#pragma unroll 8
+            for (int k = 0; k < kCopies; ++k) v += hist[b * kCopies + ((k + b) & (kCopies - 1))];
+            if (v) atomicAdd(&counts[b], v);
+        }
+    }
+}
+
 __global__ void moving_sum_kernel(const int32_t *__restrict__ newc, int32_t *__restrict__ mb,
                                   int32_t *__restrict__ totals, int64_t total) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
@@ -2920,6 +3082,48 @@ hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_l
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     by_format(state_bits, [&](auto tag) { sweep_class<decltype(tag)>(P, klass, lds_bytes, grid, stream); });
+    return hipGetLastError();
+}
+
+bool tiny_network(const Compiled &g, int32_t m) {
+    if (!g.tiny) return false;
+    const int64_t mq = ((int64_t)m + 3) / 4;
+    return g.n * mq * 64 * g.quad_bytes <= kTinyWaveBytes;
+}
+
+hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, int32_t *counts,
+                       hipStream_t stream) {
+    if (P.n_cols <= 0) return hipSuccess;
+    const int32_t n_bins = (int32_t)g.off[g.n];
+    const int64_t mq = ((int64_t)P.m + 3) / 4;
+    // 64 columns per wave, up to 256 where that still leaves several waves per
+    // SIMD and the columns fit the wave's part
+    int32_t groups = 1;
+    while (groups < 4 && P.n_cols / (64 * 2 * groups) >= dev::kTinyWaves &&
+           g.n * mq * 64 * 2 * groups * g.quad_bytes <= kTinyWaveBytes)
+        groups *= 2;
+    auto up16 = [](int64_t v) { return (int32_t)((v + 15) & ~int64_t(15)); };
+    dev::TinyLds O;
+    O.hist = up16(g.cond_words * 4);
+    O.waves = O.hist + (counts ? up16((int64_t)n_bins * dev::kCopies * 4) : 0);
+    O.list = up16((int64_t)g.n * groups * 8);
+    O.states = O.list + up16((int64_t)groups * 64 * 2);
+    O.wave_bytes = O.states + up16(g.n * mq * 64 * groups * g.quad_bytes);
+    const int32_t lds = O.waves + O.wave_bytes * (dev::kBlock / 64);
+    const int64_t waves = (P.n_cols + 64 * groups - 1) / (64 * groups);
+    const dim3 grid((unsigned)((waves + dev::kBlock / 64 - 1) / (dev::kBlock / 64)));
+    by_format(g.state_bits, [&](auto tag) {
+        using ST = decltype(tag);
+        // 16-bit states have a node of more states than a threshold table takes
+        if constexpr (!std::is_same<ST, int16_t>::value) {
+            if (counts)
+                hipLaunchKernelGGL((dev::tiny_step_kernel<ST, true>), grid, dim3(dev::kBlock), lds, stream, P, O, g.n,
+                                   groups, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off, counts);
+            else
+                hipLaunchKernelGGL((dev::tiny_step_kernel<ST, false>), grid, dim3(dev::kBlock), lds, stream, P, O,
+                                   g.n, groups, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off, counts);
+        }
+    });
     return hipGetLastError();
 }
 

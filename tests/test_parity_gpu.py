@@ -262,6 +262,34 @@ def test_wide_chunks(n_cols, m):
     H.compare_states(gpu, ref, res["flags"], color, n_cols, obs=ob)
 
 
+@pytest.mark.parametrize("n_cols,m", [(1, 1), (64, 3), (65, 8), (1021, 20), (300_000, 1), (600_001, 2)])
+@pytest.mark.parametrize("bits", [0, 4])
+def test_small_network_step(n_cols, m, bits):
+    """The one-launch step of small networks (a wave takes 64, 128 or 256
+    columns; at m = 20 and 14 nodes of byte states a wave's columns still fit,
+    at m = 200 they do not): states as the oracle draws them, counts and moving
+    sum of the drawn states bit-exact, observed entries, columns past n_cols
+    and the other path's states untouched."""
+    parents = [[], [], [0], [0, 1], [3], [2], [4, 5], [], [7], [7], [8], [9], [6], [10]]
+    card = [2, 2, 2, 3, 2, 2, 3, 4, 2, 2, 2, 2, 2, 3]
+    for mm in ((m,) if n_cols > 64 else (m, 200)):
+        net, st, ob, th = _custom(parents, card, n_cols, mm, 0.5, n_cols)
+        ctx = H.context_for(net, state_bits=bits)
+        color = oracle.graph(net.parents, net.card)["color"]
+        d_st, d_th = H.to_device(ctx, st), torch.from_numpy(th.astype(np.float32)).cuda()
+        mb, tot = (torch.zeros(ctx.cpt_total, dtype=torch.int32, device="cuda") for _ in range(2))
+        same.same_step(ctx, d_st, torch.from_numpy(ob).cuda(), d_th, mm, n_cols, st.shape[2], 0, 5, 1, mb, tot, 0,
+                       ctx.new_workspace())
+        torch.cuda.synchronize()
+        got, ref = H.from_device(ctx, d_st, mm), st.copy()
+        res = oracle.sweep(net.parents, net.card, th, color, ref, ob, mm, n_cols, 0, 5, 1, want_flags=True)
+        H.compare_states(got, ref, res["flags"], color, n_cols, obs=ob)
+        assert np.array_equal(got[:, :, n_cols:], st[:, :, n_cols:])
+        assert np.array_equal(mb.cpu().numpy(), oracle.counts(net.parents, net.card, got, mm, n_cols))
+        assert np.array_equal(tot.cpu().numpy(), mb.cpu().numpy())
+        ctx.close()
+
+
 def test_zero_columns_is_noop():
     net, st, ob, th = _custom([[], [0]], [2, 2], 8, 2, 0.5, 1, ld=8)
     ctx = H.context_for(net)
