@@ -2080,7 +2080,9 @@ __global__ __launch_bounds__(kBlock, Quad<ST>::kBytes == 2 ? 5 : Quad<ST>::kByte
 // (COUNT) and writes the latent quads back.  Bound by the start of the launch
 // and a wave's chain of draws; a launch per colour and one for the counts have
 // that start four times for the five-node student network (3 x 4.3 + 4.8 us
-// at 2,000 columns, 3 x 6.7 + 6.5 us at 100,000, m = 10).
+// at 2,000 columns, 3 x 6.7 + 6.5 us at 100,000, m = 10); this takes 11 and 20
+// us.  Measured no faster at 100,000 columns: a wave per replica quad (23 us),
+// 147 blocks of sixteen such waves (26 us).
 struct TinyLds {  // byte offsets; the rest of a wave's part at wave * wave_bytes
     int32_t hist, waves, wave_bytes, list, states;  // list, states: inside a wave's part (masks first)
 };
@@ -2138,25 +2140,54 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
     char *tile = mine + O.states;                          // state quads, [node][mq][cols]
     int32_t *hist = reinterpret_cast<int32_t *>(lds + O.hist);
     const int64_t c0 = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * cols;  // the wave's first column
+    const int64_t vstride = node_bytes<ST>(P.m, P.ld);
+    char *states = reinterpret_cast<char *>(P.states);
+    // the obs bytes of the first rows, then state rows, kRows at a time: their
+    // loads are in flight together
+    constexpr int kRows = 8;
+    auto column = [&](int g) { return c0 + 64 * g + lane; };
+    uint8_t ob[kRows];
+    auto obs_load = [&](int r0) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            if (r0 + r >= n * groups) break;  // uniform
+            const int i = (r0 + r) / groups, g = (r0 + r) % groups;
+            const int64_t j = column(g);
+            ob[r] = P.obs[(int64_t)i * P.ld + (j < P.n_cols ? j : 0)];
+        }
+    };
+    obs_load(0);
+    for (int g = 0; g < groups; ++g) {
+        const int64_t j = column(g);
+        const bool in = j < P.n_cols;
+        const char *src = states + quad_boff<ST>(0, P.ld, in ? j : 0);
+        char *dst = tile + (64 * g + lane) * Q::kBytes;
+        for (int r0 = 0; r0 < n * mq; r0 += kRows) {  // row node * mq + quad
+            typename Q::V v[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                if (r0 + r >= n * mq) break;
+                v[r] = Q::load_at(src + (int64_t)(r0 + r) * P.ld * Q::kBytes);
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                if (r0 + r >= n * mq) break;
+                if (in) Q::store_at(dst + (r0 + r) * cols * Q::kBytes, v[r]);
+            }
+        }
+    }
+    for (int r0 = 0; r0 < n * groups; r0 += kRows) {
+        if (r0 > 0) obs_load(r0);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            if (r0 + r >= n * groups) break;
+            const uint64_t lat = __ballot(ob[r] == 0 && column((r0 + r) % groups) < P.n_cols);
+            if (lane == 0) masks[r0 + r] = lat;
+        }
+    }
     for (int i = threadIdx.x; i < cond_words; i += kBlock) reinterpret_cast<uint32_t *>(lds)[i] = P.cond[i];
     if (COUNT)
         for (int i = threadIdx.x; i < n_bins * kCopies; i += kBlock) hist[i] = 0;
-    const int64_t vstride = node_bytes<ST>(P.m, P.ld);
-    char *states = reinterpret_cast<char *>(P.states);
-    for (int i = 0; i < n; ++i)
-        for (int g = 0; g < groups; ++g) {
-            const int64_t j = c0 + 64 * g + lane;
-            const bool in = j < P.n_cols;
-            const uint64_t lat = __ballot(in && P.obs[(int64_t)i * P.ld + (in ? j : 0)] == 0);
-            if (lane == 0) masks[i * groups + g] = lat;
-            const char *src = states + (int64_t)i * vstride + quad_boff<ST>(0, P.ld, in ? j : 0);
-            char *dst = tile + ((int64_t)i * mq * cols + 64 * g + lane) * Q::kBytes;
-#pragma unroll 4
-            for (int rq = 0; rq < mq; ++rq) {
-                const typename Q::V v = Q::load_at(src + (int64_t)rq * P.ld * Q::kBytes);
-                if (in) Q::store_at(dst + rq * cols * Q::kBytes, v);
-            }
-        }
     __syncthreads();
     if (c0 < P.n_cols) {
         for (int o = 0; o < n; ++o) {
