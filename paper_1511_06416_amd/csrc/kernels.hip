@@ -2090,9 +2090,9 @@ struct TinyLds {  // byte offsets; the rest of a wave's part at wave * wave_byte
 // The draws of one node's items over the wave's columns.
 template <int KT, typename ST>
 __device__ __forceinline__ void tiny_node(const SweepParams &P, cint32_t *d, int node, int ncl, const uint16_t *list,
-                                          char *tile, int cols, uint32_t c0, lds_char *table) {
+                                          char *tile, int cols, uint32_t c0, int q0, int mq, lds_char *table) {
     using Q = Quad<ST>;
-    const int mq = (P.m + 3) >> 2, lane = (int)threadIdx.x & 63;
+    const int lane = (int)threadIdx.x & 63;
     const float inv = 1.f / (float)ncl;
     cint32_t *g = d + d[9];
     const int n_e = g[0];
@@ -2108,8 +2108,8 @@ __device__ __forceinline__ void tiny_node(const SweepParams &P, cint32_t *d, int
             k -= ncl;
         }
         const int col = list[k], at = (rq * cols + col) * Q::kBytes;
-        const SlotMask mask = slot_mask<ST>(P.m - 4 * rq < 4 ? P.m - 4 * rq : 4);
-        const Philox4 rnd = gibbs_block(P, node, rq, (int64_t)c0 + col);
+        const SlotMask mask = slot_mask<ST>(P.m - 4 * (q0 + rq) < 4 ? P.m - 4 * (q0 + rq) : 4);
+        const Philox4 rnd = gibbs_block(P, node, q0 + rq, (int64_t)c0 + col);
         uint32_t Pk[2] = {base, base};
         for (int e = 0; e < n_e; ++e) {
             const typename Q::V v = Q::load_at(tile + g[2 + 2 * e] * row + at);
@@ -2124,7 +2124,7 @@ __device__ __forceinline__ void tiny_node(const SweepParams &P, cint32_t *d, int
 
 template <typename ST, bool COUNT>
 __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLds O, int32_t n, int32_t groups,
-                                                          int32_t cond_words, int32_t n_bins,
+                                                          int32_t quads_per_wave, int32_t cond_words, int32_t n_bins,
                                                           const int32_t *__restrict__ cdesc,
                                                           const int32_t *__restrict__ cdesc_off,
                                                           int32_t *__restrict__ counts) {
@@ -2132,14 +2132,19 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
     if (P.ids) P.sweep_id = P.ids[0];
     extern __shared__ float4 lds4[];
     char *lds = reinterpret_cast<char *>(lds4);
-    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-    const int mq = (P.m + 3) >> 2, cols = 64 * groups;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
+    const int cols = 64 * groups;
     char *mine = lds + O.waves + wave * O.wave_bytes;
     uint64_t *masks = reinterpret_cast<uint64_t *>(mine);  // latent columns, [node][group]
     uint16_t *list = reinterpret_cast<uint16_t *>(mine + O.list);
     char *tile = mine + O.states;                          // state quads, [node][mq][cols]
     int32_t *hist = reinterpret_cast<int32_t *>(lds + O.hist);
-    const int64_t c0 = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * cols;  // the wave's first column
+    // the wave's first column, and its replica quads [q0, q0 + mq)
+    const int quads = (P.m + 3) >> 2, parts = (quads + quads_per_wave - 1) / quads_per_wave;
+    const int64_t item = (int64_t)blockIdx.x * (kBlock / 64) + wave;
+    const int64_t c0 = item / parts * cols;
+    const int q0 = (int)(item % parts) * quads_per_wave;
+    const int mq = quads - q0 < quads_per_wave ? quads - q0 : quads_per_wave;
     const int64_t vstride = node_bytes<ST>(P.m, P.ld);
     char *states = reinterpret_cast<char *>(P.states);
     // the obs bytes of the first rows, then state rows, kRows at a time: their
@@ -2160,14 +2165,15 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
     for (int g = 0; g < groups; ++g) {
         const int64_t j = column(g);
         const bool in = j < P.n_cols;
-        const char *src = states + quad_boff<ST>(0, P.ld, in ? j : 0);
+        const char *src = states + quad_boff<ST>(q0, P.ld, in ? j : 0);
         char *dst = tile + (64 * g + lane) * Q::kBytes;
         for (int r0 = 0; r0 < n * mq; r0 += kRows) {  // row node * mq + quad
             typename Q::V v[kRows];
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
                 if (r0 + r >= n * mq) break;
-                v[r] = Q::load_at(src + (int64_t)(r0 + r) * P.ld * Q::kBytes);
+                const int i = (r0 + r) / mq;
+                v[r] = Q::load_at(src + i * vstride + (int64_t)(r0 + r - i * mq) * P.ld * Q::kBytes);
             }
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
@@ -2208,10 +2214,10 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
             if (ncl == 0) continue;
             lds_char *table = (lds_char *)lds4 + 4 * d[5];
             const int KT = d[7];
-            if (KT == 1) tiny_node<1, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
-            else if (KT == 2) tiny_node<2, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
-            else if (KT == 4) tiny_node<4, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
-            else tiny_node<8, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, table);
+            if (KT == 1) tiny_node<1, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
+            else if (KT == 2) tiny_node<2, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
+            else if (KT == 4) tiny_node<4, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
+            else tiny_node<8, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
             __builtin_amdgcn_wave_barrier();
         }
         const int row = mq * cols * Q::kBytes;
@@ -2228,7 +2234,7 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
                     const int at = (rq * cols + 64 * g + lane) * Q::kBytes;
                     const typename Q::V own = Q::load_at(tile + i * row + at);
                     if (write)
-                        Q::store_at(states + (int64_t)i * vstride + quad_boff<ST>(rq, P.ld, j), own);
+                        Q::store_at(states + (int64_t)i * vstride + quad_boff<ST>(q0 + rq, P.ld, j), own);
                     if constexpr (COUNT) {
                         // bins in bytes of the lane's histogram copy
                         uint32_t Pk[2], p[2];
@@ -2243,7 +2249,7 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
                         }
 #pragma unroll
                         for (int c = 0; c < 4; ++c)
-                            if (in && 4 * rq + c < P.m)
+                            if (in && 4 * (q0 + rq) + c < P.m)
                                 atomicAdd(reinterpret_cast<int32_t *>(reinterpret_cast<char *>(hist + off * kCopies) +
                                                                       packed_index<ST>(Pk, c)), 1);
                     }
@@ -3126,13 +3132,18 @@ hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, 
                        hipStream_t stream) {
     if (P.n_cols <= 0) return hipSuccess;
     const int32_t n_bins = (int32_t)g.off[g.n];
-    const int64_t mq = ((int64_t)P.m + 3) / 4;
-    // 64 columns per wave, up to 256 where that still leaves several waves per
-    // SIMD and the columns fit the wave's part
+    int64_t mq = ((int64_t)P.m + 3) / 4;
+    // 64 columns and all replica quads per wave: more columns (up to 256)
+    // where that still leaves kTinyWaves waves and they fit the wave's part,
+    // fewer quads while there are fewer than half as many waves
     int32_t groups = 1;
     while (groups < 4 && P.n_cols / (64 * 2 * groups) >= dev::kTinyWaves &&
            g.n * mq * 64 * 2 * groups * g.quad_bytes <= kTinyWaveBytes)
         groups *= 2;
+    const int64_t col_waves = (P.n_cols + 64 * groups - 1) / (64 * groups);
+    const int64_t quads = mq;
+    if (col_waves < dev::kTinyWaves / 2) mq = (mq * col_waves + dev::kTinyWaves / 2 - 1) / (dev::kTinyWaves / 2);
+    const int64_t waves = col_waves * ((quads + mq - 1) / mq);
     auto up16 = [](int64_t v) { return (int32_t)((v + 15) & ~int64_t(15)); };
     dev::TinyLds O;
     O.hist = up16(g.cond_words * 4);
@@ -3141,7 +3152,6 @@ hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, 
     O.states = O.list + up16((int64_t)groups * 64 * 2);
     O.wave_bytes = O.states + up16(g.n * mq * 64 * groups * g.quad_bytes);
     const int32_t lds = O.waves + O.wave_bytes * (dev::kBlock / 64);
-    const int64_t waves = (P.n_cols + 64 * groups - 1) / (64 * groups);
     const dim3 grid((unsigned)((waves + dev::kBlock / 64 - 1) / (dev::kBlock / 64)));
     by_format(g.state_bits, [&](auto tag) {
         using ST = decltype(tag);
@@ -3149,10 +3159,11 @@ hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, 
         if constexpr (!std::is_same<ST, int16_t>::value) {
             if (counts)
                 hipLaunchKernelGGL((dev::tiny_step_kernel<ST, true>), grid, dim3(dev::kBlock), lds, stream, P, O, g.n,
-                                   groups, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off, counts);
+                                   groups, (int32_t)mq, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off, counts);
             else
                 hipLaunchKernelGGL((dev::tiny_step_kernel<ST, false>), grid, dim3(dev::kBlock), lds, stream, P, O,
-                                   g.n, groups, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off, counts);
+                                   g.n, groups, (int32_t)mq, (int32_t)g.cond_words, n_bins, t.cdesc, t.cdesc_off,
+                                   counts);
         }
     });
     return hipGetLastError();

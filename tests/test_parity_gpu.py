@@ -262,11 +262,11 @@ def test_wide_chunks(n_cols, m):
     H.compare_states(gpu, ref, res["flags"], color, n_cols, obs=ob)
 
 
-@pytest.mark.parametrize("n_cols,m", [(1, 1), (64, 3), (65, 8), (1021, 20), (300_000, 1), (600_001, 2)])
+@pytest.mark.parametrize("n_cols,m", [(1, 1), (64, 3), (65, 8), (1021, 20), (20_003, 20), (300_000, 1), (600_001, 2)])
 @pytest.mark.parametrize("bits", [0, 4])
 def test_small_network_step(n_cols, m, bits):
     """The one-launch step of small networks (a wave takes 64, 128 or 256
-    columns; at m = 20 and 14 nodes of byte states a wave's columns still fit,
+    columns, one, two or all replica quads of them; at m = 20 and 14 nodes of byte states a wave's columns still fit,
     at m = 200 they do not): states as the oracle draws them, counts and moving
     sum of the drawn states bit-exact, observed entries, columns past n_cols
     and the other path's states untouched."""
