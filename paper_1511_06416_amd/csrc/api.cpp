@@ -329,10 +329,14 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
         if (counted) *counted = counts != nullptr;
         return check_hip(same::launch_tiny(P, t, g, counts, s), "small-network launch");
     }
-    StreamRes *sr = nullptr;
-    int rc = stream_res_for_current_device(ctx, &sr);
-    if (rc) return rc;
     const int32_t L = same::kLaunchClasses;
+    // only a network with class-1 nodes forks: creating the streams and events
+    // takes about 0.4 ms of a context's first sweep
+    bool forks = false;
+    for (int32_t c = 0; c < g.n_colors; ++c) forks |= g.launch[c * (L + 1) + 2] > g.launch[c * (L + 1) + 1];
+    StreamRes *sr = nullptr;
+    int rc = forks ? stream_res_for_current_device(ctx, &sr) : SAME_OK;
+    if (rc) return rc;
     for (int32_t c = 0; c < g.n_colors; ++c) {
         P.reverse = c & 1;
         // the nodes of one colour are independent: the global-table launch
