@@ -2390,12 +2390,11 @@ __device__ __forceinline__ void resample_draws(ResampleShared &S, int64_t base, 
         S.gam[x] = gamma_mt(S.shape[x], (uint32_t)(base + x), u, k0, k1, ub);
         S.sums[x] = ub;
     }
-    if (alpha < 1.0) {  // the boost of shapes below one (all of them listed, each by this lane)
-        for (int l = tid; l < n_list; l += kResampleBlock) {
-            const int x = S.list[l];
-            const double a = S.shape[x];
-            if (a < 1.0) S.gam[x] *= pow(S.sums[x], 1.0 / a);
-        }
+    // the boost of shapes below one (all of them listed, each by this lane)
+    for (int l = tid; l < n_list; l += kResampleBlock) {
+        const int x = S.list[l];
+        const double a = S.shape[x];
+        if (a < 1.0) S.gam[x] *= pow(S.sums[x], 1.0 / a);
     }
     __syncthreads();
 }

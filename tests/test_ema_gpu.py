@@ -55,6 +55,30 @@ def test_sample_cpts_ema_matches_oracle(cfg):
     ctx.close()
 
 
+@pytest.mark.parametrize("prior", [1.0, 1.5])
+def test_shapes_below_one_with_negative_totals(prior):
+    """A shape prior + total below one draws with its boost factor whatever the
+    prior is: fp64 totals in (-1, 0), and the integer entry point's totals of
+    -1 (shape 0.5 at prior 1.5)."""
+    net = make_workload(3, n_cols=8, minibatches=[]).net
+    ctx = H.context_for(net, prior=prior)
+    ws = ctx.new_workspace()
+    tot = np.random.default_rng(8).random(ctx.cpt_total) * 2.0 - 0.95
+    got = torch.empty(ctx.cpt_total, dtype=torch.float32, device="cuda")
+    calls = [(same.same_sample_cpts_ema, oracle.dirichlet_f64, tot)]
+    if prior > 1.0:
+        calls.append((same.same_sample_cpts, oracle.dirichlet, np.round(tot).astype(np.int32)))
+    for call, ref, t in calls:
+        assert (prior + t < 1.0).any() and (prior + t > 0.0).all()
+        want = ref(net.parents, net.card, t, prior, 33, 9)
+        call(ctx, torch.from_numpy(t).cuda(), got, 33, 9, ws)
+        torch.cuda.synchronize()
+        # the bar of the resample: equal but for the last bit of the fp64 functions
+        assert np.mean(got.cpu().numpy() == want) >= 1 - 1e-5
+        np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-6, atol=0)
+    ctx.close()
+
+
 @pytest.mark.parametrize("bits", [0, 4], ids=["8bit", "4bit"])
 def test_stream_pass_ema_equals_resident(bits):
     w = make_workload(3, n_cols=9_001, nb=3_000, m=3)
