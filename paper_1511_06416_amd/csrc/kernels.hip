@@ -2087,6 +2087,15 @@ struct TinyLds {  // byte offsets; the rest of a wave's part at wave * wave_byte
     int32_t hist, waves, wave_bytes, list, states;  // list, states: inside a wave's part (masks first)
 };
 
+// Lanes of a wave exchange data through LDS: what they wrote before is seen
+// after.  The wave's LDS operations stay in program order, so the fences only
+// bind the compiler (no instruction, at most a wait).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The draws of one node's items over the wave's columns.
 template <int KT, typename ST>
 __device__ __forceinline__ void tiny_node(const SweepParams &P, cint32_t *d, int node, int ncl, const uint16_t *list,
@@ -2208,9 +2217,8 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
                         (uint16_t)(64 * g + lane);
                 ncl += __builtin_popcountll(lat);
             }
-            // the wave's LDS operations stay in program order: the list, then
-            // its reads; a node's draws, then the next colour's reads
-            __builtin_amdgcn_wave_barrier();
+            // the list, then its reads by other lanes
+            wave_lds_sync();
             if (ncl == 0) continue;
             lds_char *table = (lds_char *)lds4 + 4 * d[5];
             const int KT = d[7];
@@ -2218,7 +2226,9 @@ __global__ __launch_bounds__(kBlock) void tiny_step_kernel(SweepParams P, TinyLd
             else if (KT == 2) tiny_node<2, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
             else if (KT == 4) tiny_node<4, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
             else tiny_node<8, ST>(P, d, node, ncl, list, tile, cols, (uint32_t)c0, q0, mq, table);
-            __builtin_amdgcn_wave_barrier();
+            // a node's draws, then the next colour's reads; the list's reads,
+            // then the next list
+            wave_lds_sync();
         }
         const int row = mq * cols * Q::kBytes;
         for (int i = 0; i < n; ++i) {
