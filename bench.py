@@ -426,6 +426,7 @@ def sweep_roofline(w, net, mbs, hidden, node_samples, kt, elapsed, args, copy_gb
     global-table launches (class 1, beside class 0 on a second stream) and the
     colour phases (the sweep's own device time, all classes)."""
     import numpy as np
+    import paper_1511_06416_amd as same
     assert kt["launches"][2] == 0 and kt["launches"][3] == 0, \
         "this workload is expected to run entirely in the fast sweep kernel"
     bytes_per_ns = bytes_per_node_sample(ctx, hidden, w.m)
@@ -444,9 +445,13 @@ def sweep_roofline(w, net, mbs, hidden, node_samples, kt, elapsed, args, copy_gb
     traffic = measured_traffic(args.cfg, ctx.state_bits)
     avg_ms = ms0 / n0
     phase_s = kt["phase_ms"] / 1e3
+    # a small network's step draws all colours and counts in one launch per tile
+    one_launch = same.same_sweep_plan(ctx, w.m, 4)[1] < ctx.sweep_launches
+    kernel = ("tiny_step_kernel<%s, true> (all colours and the counts in one launch" if one_launch else
+              "sweep_fast_kernel<%s, false, true> (tables staged in LDS, whole or in part") % state_type_name(
+                  ctx.state_bits) + "; every launch of the timed passes)"
     out = {
-        "kernel": "sweep_fast_kernel<%s, false, true> (tables staged in LDS, whole or in part; "
-                  "every launch of the timed passes)" % state_type_name(ctx.state_bits),
+        "kernel": kernel,
         "bound": "hbm",
         "achieved": round(hbm, 1),
         "peak": HBM_PEAK_GBS,

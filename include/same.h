@@ -89,7 +89,8 @@ typedef struct {
     int32_t state_bytes;  /* bytes of one state in the element arrays (CSR values, targets,
                              compact host states): 1, or 2 for 16-bit states */
     int32_t max_card;     /* largest K_i */
-    int32_t sweep_launches;  /* sweep kernel launches per same_sweep call */
+    int32_t sweep_launches;  /* sweep kernel launches per column tile, colour by colour (a small
+                                network draws its colours in one launch: see same_sweep_plan) */
     int32_t table_nodes;     /* nodes drawing from precomputed threshold tables */
     int32_t state_bits;      /* bits per state in the states array: 4, 8 or 16 (see States) */
 } same_layout_t;
@@ -189,7 +190,7 @@ int same_workspace_size(const same_ctx *ctx, size_t *bytes);
  * pointers.
  * col_offset and ld must be multiples of 4 and states/obs 4-byte aligned.
  * seed and sweep_id select the Philox stream.  The colour groups launch in
- * order on `stream`.  Inside a group, the nodes whose tables are read from
+ * order on `stream` (a small network's in one launch, see same_sweep_plan).  Inside a group, the nodes whose tables are read from
  * global memory (launch class 1) run on a side stream that the context keeps
  * per device, forked from and joined back into `stream` with events, beside
  * the group's LDS-staged launch; the call's work is still ordered on `stream`
@@ -274,7 +275,10 @@ int same_sample_cpts(same_ctx *ctx, const int32_t *totals, float *cpts_out, uint
 /*
  * How same_sweep splits a minibatch of n_cols columns with m replicas: the
  * column-tile width and the number of sweep-kernel launches per call (for
- * profiling; host only).
+ * profiling; host only): per tile one for each launch class of each colour
+ * group, or a single one for all colours of a small network (few nodes, all on
+ * threshold tables, and few replicas), which same_step makes do its counts
+ * too.
  */
 int same_sweep_plan(const same_ctx *ctx, int32_t m, int64_t n_cols, int64_t *tile_cols,
                     int32_t *launches);
@@ -479,7 +483,9 @@ int same_grow_replicas(same_ctx *ctx, const void *states, int32_t m, void *dst, 
  * replica) slots those launches covered since timing was enabled, and the
  * summed device milliseconds of the colour phases (one per colour group and
  * column tile: from before the group's first launch to after its last, on
- * the caller's stream).  A group's class-1 launch runs beside its class-0
+ * the caller's stream).  A small network's single launch (see
+ * same_sweep_plan) is one class-0 launch and one phase; within same_step its
+ * time includes the counts.  A group's class-1 launch runs beside its class-0
  * launch (see same_sweep), so the per-class sums count their shared time
  * twice and phase_ms is the sweep's own device time.  Host calls; the waits
  * make them unsuitable inside a captured or latency-critical sequence.
@@ -499,7 +505,8 @@ int same_kernel_times(same_ctx *ctx, same_kernel_times_t *out);
  * Replayable step graphs (Sec. 4 fuses colour groups into few large kernel
  * calls to hide the GPU's per-kernel overhead; on a small minibatch the
  * launches of one step -- table builds, one or two sweep launches per
- * colour group, counts, moving sum, Gamma and normalisation -- cost more
+ * colour group, the counts, the Dirichlet resample with the moving sum; on a
+ * small network one launch for the colours and the counts -- cost more
  * than their work).  same_step_graph captures `steps` consecutive same_step
  * calls over one resident minibatch into a HIP graph; same_graph_launch
  * replays it on `stream` with one launch.

@@ -310,6 +310,21 @@ int prepare_sweep(same_ctx *ctx, same::DeviceTables *t, void *states, const uint
     return SAME_OK;
 }
 
+// Brackets launches on `s` with a pair of events when they are timed (klass
+// < 0: a colour phase).
+int timing_begin(KernelTiming::Rec &rec, hipStream_t s) {
+    int rc = check_hip(hipEventCreate(&rec.start), "hipEventCreate");
+    if (!rc) rc = check_hip(hipEventCreate(&rec.end), "hipEventCreate");
+    if (!rc) rc = check_hip(hipEventRecord(rec.start, s), "hipEventRecord");
+    return rc;
+}
+
+int timing_end(same_ctx *ctx, const KernelTiming::Rec &rec, hipStream_t s) {
+    int rc = check_hip(hipEventRecord(rec.end, s), "hipEventRecord");
+    if (!rc) ctx->timing.pending.push_back(rec);
+    return rc;
+}
+
 // All colour groups over columns [t0, t0 + nt) of the minibatch described by
 // P.  A small network's single launch adds the tile's histograms to counts
 // (nullable), which *counted reports; the others leave the counts to the
@@ -324,10 +339,18 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
     P.col_offset = P0.col_offset + t0;
     P.win_begin = P0.win_begin - t0;
     if (counted) *counted = false;
-    // per-launch timing reports the colour launches
-    if (P.win == 0 && !ctx->timing.on && same::tiny_network(g, P.m)) {
+    if (P.win == 0 && same::tiny_network(g, P.m)) {
         if (counted) *counted = counts != nullptr;
-        return check_hip(same::launch_tiny(P, t, g, counts, s), "small-network launch");
+        // timed as one class-0 launch and one colour phase
+        KernelTiming::Rec phase{-1, 1, nullptr, nullptr, 0.0};
+        KernelTiming::Rec rec{0, 1, nullptr, nullptr, (double)g.n * (double)nt * (double)P.m};
+        const bool timed = ctx->timing.on && nt > 0;
+        int rc = timed ? timing_begin(phase, s) : SAME_OK;
+        if (!rc && timed) rc = timing_begin(rec, s);
+        if (!rc) rc = check_hip(same::launch_tiny(P, t, g, counts, s), "small-network launch");
+        if (!rc && timed) rc = timing_end(ctx, rec, s);
+        if (!rc && timed) rc = timing_end(ctx, phase, s);
+        return rc;
     }
     const int32_t L = same::kLaunchClasses;
     // only a network with class-1 nodes forks: creating the streams and events
@@ -346,9 +369,7 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
         KernelTiming::Rec phase{-1, 1, nullptr, nullptr, 0.0};
         const bool phase_timed = ctx->timing.on && nt > 0 && g.launch[c * (L + 1) + L] > g.launch[c * (L + 1)];
         if (phase_timed) {
-            rc = check_hip(hipEventCreate(&phase.start), "hipEventCreate");
-            if (!rc) rc = check_hip(hipEventCreate(&phase.end), "hipEventCreate");
-            if (!rc) rc = check_hip(hipEventRecord(phase.start, s), "hipEventRecord");
+            rc = timing_begin(phase, s);
             if (rc) return rc;
         }
         if (fork) {
@@ -362,9 +383,7 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
             KernelTiming::Rec rec{k, 1, nullptr, nullptr, (double)(e - b) * (double)nt * (double)P.m};
             const bool timed = ctx->timing.on && e > b && nt > 0;
             if (timed) {
-                rc = check_hip(hipEventCreate(&rec.start), "hipEventCreate");
-                if (!rc) rc = check_hip(hipEventCreate(&rec.end), "hipEventCreate");
-                if (!rc) rc = check_hip(hipEventRecord(rec.start, ls), "hipEventRecord");
+                rc = timing_begin(rec, ls);
                 if (rc) return rc;
             }
             rc = check_hip(same::launch_sweep(P, b, e - b, g.launch_long[c * L + k], k, g.launch_lds[c * L + k],
@@ -372,9 +391,8 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
                            "sweep launch");
             if (rc) return rc;
             if (timed) {
-                rc = check_hip(hipEventRecord(rec.end, ls), "hipEventRecord");
+                rc = timing_end(ctx, rec, ls);
                 if (rc) return rc;
-                ctx->timing.pending.push_back(rec);
             }
         }
         if (fork) {
@@ -383,9 +401,8 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
             if (rc) return rc;
         }
         if (phase_timed) {
-            rc = check_hip(hipEventRecord(phase.end, s), "hipEventRecord");
+            rc = timing_end(ctx, phase, s);
             if (rc) return rc;
-            ctx->timing.pending.push_back(phase);
         }
     }
     return SAME_OK;
@@ -695,7 +712,9 @@ int same_sweep_plan(const same_ctx *ctx, int32_t m, int64_t n_cols, int64_t *til
     same_layout_t lay;
     same_layout(ctx, &lay, nullptr, nullptr);
     *tile_cols_out = T;
-    *launches = (int32_t)(((n_cols + T - 1) / T) * lay.sweep_launches);
+    // a small network's colours are one launch per tile
+    const int32_t per_tile = same::tiny_network(ctx->g, m) ? 1 : lay.sweep_launches;
+    *launches = (int32_t)(((n_cols + T - 1) / T) * per_tile);
     return SAME_OK;
 }
 

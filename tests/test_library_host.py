@@ -250,6 +250,19 @@ def test_kernel_class_options_keep_layout(cfg, kw):
         assert b.sweep_launches >= a.sweep_launches
 
 
+def test_sweep_plan_launches():
+    """One launch per tile for a small network, one per (colour, class) and tile
+    for the others, among them a small network with too many replicas."""
+    small, big = _ctx(koller()), _ctx(make_network(3))
+    assert small.sweep_launches == small.n_colors == 3
+    assert same.same_sweep_plan(small, 1, 2_000) == (2_000, 1)
+    assert same.same_sweep_plan(small, 65_535, 100) == (100, 3)
+    assert same.same_sweep_plan(big, 1, 2_000) == (2_000, big.sweep_launches)
+    pptr, pidx, card = koller().csr()
+    tiled = same.same_create_ex(pptr, pidx, card, 1.0, tile_bytes=1)  # 1024-column tiles
+    assert same.same_sweep_plan(tiled, 1, 2_500) == (1024, 3)
+
+
 def test_kernel_timing_host_calls():
     ctx = _ctx(koller())
     assert same.same_kernel_times(ctx) == {"ms": [0.0] * 4, "launches": [0] * 4, "phase_ms": 0.0, "phases": 0,

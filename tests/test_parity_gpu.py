@@ -615,6 +615,35 @@ def test_kernel_timing_counts_launches_and_phases():
                                            "node_samples": [0.0] * 4}
 
 
+def test_kernel_timing_of_a_small_network():
+    """Timing reports the launches that the untimed calls make: a small
+    network's one launch per tile, as class 0 and as one phase, in the sweep and
+    in the step; the results do not change."""
+    w = make_workload(1)
+    ctx = H.context_for(w.net, tile_bytes=1)
+    cols = w.mb_cols(0)
+    launches = same.same_sweep_plan(ctx, w.m, cols)[1]
+    assert launches == 2
+    outs = []
+    for timed in (False, True):
+        st, ob = H.to_device(ctx, w.states[0]), w.obs[0].cuda()
+        th = torch.from_numpy(w.init_theta).cuda()
+        mb, tot = (torch.zeros(ctx.cpt_total, dtype=torch.int32, device="cuda") for _ in range(2))
+        ws = ctx.new_workspace()
+        same.same_kernel_timing(ctx, timed)
+        same.same_sweep(ctx, st, ob, th, w.m, cols, w.ld, 0, w.seed, 0, ws)
+        same.same_step(ctx, st, ob, th, w.m, cols, w.ld, 0, w.seed, 1, mb, tot, 0, ws)
+        torch.cuda.synchronize()
+        outs.append([x.cpu().numpy() for x in (st, mb, tot, th)])
+    kt = same.same_kernel_times(ctx)
+    same.same_kernel_timing(ctx, False)
+    assert kt["launches"] == [2 * launches, 0, 0, 0] and kt["phases"] == 2 * launches
+    assert kt["node_samples"][0] == 2.0 * w.net.n * cols * w.m
+    assert kt["phase_ms"] >= kt["ms"][0] > 0.0
+    for x, y in zip(*outs):
+        assert np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("big", [False, True], ids=["int8", "int16"])
 def test_tiled_step_counts_with_unaligned_rows(big):
     """same_step over 1024-column tiles with rows of ld = 5004 (not a multiple
