@@ -263,6 +263,25 @@ def test_sweep_plan_launches():
     assert same.same_sweep_plan(tiled, 1, 2_500) == (1024, 3)
 
 
+@pytest.mark.parametrize("parents,card,one", [
+    ([[], [0], [1], [2], [3], [4]], [2] * 6, False),                   # six nodes in two groups
+    ([[], [0], [1], [2]], [2] * 4, True),                              # four in two
+    ([[], [0], [0, 1], [2], [2], [3]], [2, 3, 2, 4, 2, 2], True),      # six in three
+    ([[], [0], [0, 1], [2], [2], [3], [3]], [2] * 7, False),           # seven nodes
+    ([[], [], []], [2] * 3, False),                                    # three nodes in one group
+    ([[], [0], [0, 1]], [4, 4, 4], False),                             # 84 CPT entries
+    ([[i - 1] if i else [] for i in range(24)], [2] * 24, False),
+])
+def test_small_network_rule(parents, card, one):
+    """Networks of few nodes per colour group take one sweep launch; chaining
+    more nodes in one launch is slower than a launch per group."""
+    pptr = np.cumsum([0] + [len(p) for p in parents]).astype(np.int32)
+    pidx = np.array([p for ps in parents for p in ps], dtype=np.int32)
+    ctx = same.same_create(pptr, pidx, np.array(card, np.int32))
+    assert ctx.table_nodes == len(card)
+    assert same.same_sweep_plan(ctx, 4, 2_000)[1] == (1 if one else ctx.n_colors)
+
+
 def test_kernel_timing_host_calls():
     ctx = _ctx(koller())
     assert same.same_kernel_times(ctx) == {"ms": [0.0] * 4, "launches": [0] * 4, "phase_ms": 0.0, "phases": 0,

@@ -262,32 +262,65 @@ def test_wide_chunks(n_cols, m):
     H.compare_states(gpu, ref, res["flags"], color, n_cols, obs=ob)
 
 
-@pytest.mark.parametrize("n_cols,m", [(1, 1), (64, 3), (65, 8), (1021, 20), (20_003, 20), (300_000, 1), (600_001, 2)])
+def _small_network_geometry(n, quad_bytes, m, n_cols):
+    """(64-column groups of a wave, replica quads of a wave, replica quads) of
+    the one-launch step."""
+    quads, groups = (m + 3) // 4, 1
+    while groups < 4 and n_cols // (128 * groups) >= 2048 and n * quads * 128 * groups * quad_bytes <= 8192:
+        groups *= 2
+    waves = -(-n_cols // (64 * groups))
+    return groups, quads if waves >= 1024 else -(-quads * waves // 1024), quads
+
+
+STUDENT = [[], [], [0], [0, 1], [3]], [2, 2, 2, 3, 2]
+SIX = [[], [0], [0, 1], [2], [2], [3]], [2, 3, 2, 4, 2, 2]
+PAIR = [[], [0]], [9, 5]             # eight thresholds per configuration
+
+
+@pytest.mark.parametrize("net,n_cols,m,geometry", [
+    (STUDENT, 1, 1, (1, 1, 1)),
+    (STUDENT, 65, 8, (1, 1, 2)),
+    (SIX, 1021, 20, (1, 1, 5)),
+    (PAIR, 1500, 6, (1, 1, 2)),
+    (STUDENT, 25_002, 20, (1, 2, 5)),      # waves of two, two and one quads
+    (STUDENT, 35_001, 10, (1, 2, 3)),      # a last part of one quad, half padding
+    (SIX, 36_003, 18, (1, 3, 5)),          # waves of three and two quads
+    (STUDENT, 100_001, 10, (1, 3, 3)),     # all quads
+    (PAIR, 70_001, 13, (1, 4, 4)),
+    (STUDENT, 262_209, 10, (2, 3, 3)),     # 128 columns a wave
+    (SIX, 270_001, 6, (2, 2, 2)),
+    (STUDENT, 600_001, 2, (4, 1, 1)),      # 256 columns
+    (STUDENT, 530_001, 5, None),           # 256 columns in 4 bits, 128 in bytes
+    (STUDENT, 200, 200, None),             # too many replicas for a wave: the colour launches
+])
 @pytest.mark.parametrize("bits", [0, 4])
-def test_small_network_step(n_cols, m, bits):
-    """The one-launch step of small networks (a wave takes 64, 128 or 256
-    columns, one, two or all replica quads of them; at m = 20 and 14 nodes of byte states a wave's columns still fit,
-    at m = 200 they do not): states as the oracle draws them, counts and moving
-    sum of the drawn states bit-exact, observed entries, columns past n_cols
-    and the other path's states untouched."""
-    parents = [[], [], [0], [0, 1], [3], [2], [4, 5], [], [7], [7], [8], [9], [6], [10]]
-    card = [2, 2, 2, 3, 2, 2, 3, 4, 2, 2, 2, 2, 2, 3]
-    for mm in ((m,) if n_cols > 64 else (m, 200)):
-        net, st, ob, th = _custom(parents, card, n_cols, mm, 0.5, n_cols)
-        ctx = H.context_for(net, state_bits=bits)
-        color = oracle.graph(net.parents, net.card)["color"]
-        d_st, d_th = H.to_device(ctx, st), torch.from_numpy(th.astype(np.float32)).cuda()
-        mb, tot = (torch.zeros(ctx.cpt_total, dtype=torch.int32, device="cuda") for _ in range(2))
-        same.same_step(ctx, d_st, torch.from_numpy(ob).cuda(), d_th, mm, n_cols, st.shape[2], 0, 5, 1, mb, tot, 0,
-                       ctx.new_workspace())
-        torch.cuda.synchronize()
-        got, ref = H.from_device(ctx, d_st, mm), st.copy()
-        res = oracle.sweep(net.parents, net.card, th, color, ref, ob, mm, n_cols, 0, 5, 1, want_flags=True)
-        H.compare_states(got, ref, res["flags"], color, n_cols, obs=ob)
-        assert np.array_equal(got[:, :, n_cols:], st[:, :, n_cols:])
-        assert np.array_equal(mb.cpu().numpy(), oracle.counts(net.parents, net.card, got, mm, n_cols))
-        assert np.array_equal(tot.cpu().numpy(), mb.cpu().numpy())
-        ctx.close()
+def test_small_network_step(net, n_cols, m, geometry, bits):
+    """The one-launch step of small networks, at the columns and replica quads a
+    wave takes (asserted, so that a case reaches what it names): states as the
+    oracle draws them, counts and moving sum of the drawn states bit-exact,
+    observed entries and columns past n_cols untouched."""
+    parents, card = net
+    quad_bytes = 2 if bits == 4 else 4
+    if geometry is not None:
+        assert _small_network_geometry(len(card), quad_bytes, m, n_cols) == geometry
+    elif m == 5:
+        assert _small_network_geometry(len(card), quad_bytes, m, n_cols) == (4 if bits == 4 else 2, 2, 2)
+    net, st, ob, th = _custom(parents, card, n_cols, m, 0.5, n_cols)
+    ctx = H.context_for(net, state_bits=bits)
+    assert same.same_sweep_plan(ctx, m, n_cols)[1] == (ctx.n_colors if m == 200 else 1)
+    color = oracle.graph(net.parents, net.card)["color"]
+    d_st, d_th = H.to_device(ctx, st), torch.from_numpy(th.astype(np.float32)).cuda()
+    mb, tot = (torch.zeros(ctx.cpt_total, dtype=torch.int32, device="cuda") for _ in range(2))
+    same.same_step(ctx, d_st, torch.from_numpy(ob).cuda(), d_th, m, n_cols, st.shape[2], 0, 5, 1, mb, tot, 0,
+                   ctx.new_workspace())
+    torch.cuda.synchronize()
+    got, ref = H.from_device(ctx, d_st, m), st.copy()
+    res = oracle.sweep(net.parents, net.card, th, color, ref, ob, m, n_cols, 0, 5, 1, want_flags=True)
+    H.compare_states(got, ref, res["flags"], color, n_cols, obs=ob)
+    assert np.array_equal(got[:, :, n_cols:], st[:, :, n_cols:])
+    assert np.array_equal(mb.cpu().numpy(), oracle.counts(net.parents, net.card, got, m, n_cols))
+    assert np.array_equal(tot.cpu().numpy(), mb.cpu().numpy())
+    ctx.close()
 
 
 def test_zero_columns_is_noop():
