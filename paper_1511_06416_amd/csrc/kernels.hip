@@ -3116,12 +3116,24 @@ hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_l
                          dev::kMinLightSplit);
         n_geom = n_long > 0 && n_long < count ? 2 : 1;
     } else {
-        // of few replica quads a block takes more columns, so that its lanes
-        // have as many items and a column slab of a row as many bytes: 100
-        // nodes x 1M columns, m = 5, 837 -> 805 us per step with 2048
-        // columns; three quads keep 1024 (1000-node network 4.76 ms, 5.14 with
-        // 2048: the slab's rows no longer stay in L2)
-        const int64_t wide = klass != 0 ? block_quads : block_quads * (m_quads <= 1 ? 4 : m_quads == 2 ? 2 : 1);
+        // A class-0 block of few replica quads takes up to four times the
+        // columns, so that its lanes have as many items as with three quads:
+        // while its part of a row (all replica quads) stays within 8 KB, the
+        // launch has enough blocks and, with two quads, enough rounds of slabs
+        // over the XCDs that the last one, partly empty, costs less.  100 nodes
+        // x 1M columns, us per step with 1024 / 2048 / 4096 columns: 4-bit
+        // states, one quad 509 / 451 / 455, two quads 778 / 748; bytes, one
+        // quad 617 / 586 / 620, two quads 1064 / 1119; 16-bit, one quad 1674 /
+        // 1725 / 1777.  4-bit, two quads, rounds at 2048 columns: 61 0.960 of
+        // the time with 1024, 12 0.98-0.99 (500 nodes x 200,000), 6 1.02-1.03
+        // (1000 x 100,000), 9 1.09 (300 x 150,000, 3700 blocks).  Three quads,
+        // 1000 nodes x 250,000: 4760 / 5140.
+        int64_t wide = block_quads;
+        if (klass == 0)
+            while (wide < 4 * block_quads && 2 * wide * 4 * m_quads * (state_bits / 2) <= 8192 &&
+                   count * chunks_of(2 * wide) >= dev::kMinSweepBlocks &&
+                   (m_quads == 1 || chunks_of(2 * wide) >= 12 * (int64_t)dev::kXcds))
+                wide *= 2;
         P.geom[0] = geometry(begin, count, wide, klass == 3 ? dev::kMinGenQuads : dev::kMinSweepQuads,
                              dev::kMinSweepBlocks, dev::kMinSweepBlocks);
     }

@@ -246,16 +246,50 @@ def test_group_records(n_kids, n_par, bits):
     _custom_case(net, st, ob, th, 6, 777, win=(0, 64), table_limit=0, **(dict(state_bits=4) if bits == 4 else {}))
 
 
-@pytest.mark.parametrize("n_cols,m", [(70_000, 3), (70_000, 6), (4_099, 2), (150_003, 1)])
-def test_wide_chunks(n_cols, m):
-    """Blocks that list up to four column quads per lane (one replica quad),
-    two (two quads) and one, in launches of 4096 blocks and more, and a small
-    launch whose long and short items take different chunks."""
+def _sweep_chunk(count, m, n_cols, quad_bytes):
+    """Column quads of a block for `count` fully staged nodes of one colour;
+    None for a launch too small to fill the device."""
+    quads, mq, wide = (n_cols + 3) // 4, (m + 3) // 4, 256
+    if count * -(-quads // 256) * mq < 4096:
+        return None
+    while wide < 1024 and 2 * wide * 4 * mq * quad_bytes <= 8192:
+        chunks = -(-quads // (2 * wide))
+        if count * chunks < 4096 or (mq > 1 and chunks < 96):
+            break
+        wide *= 2
+    return wide
+
+
+@pytest.mark.parametrize("bits,m,h,n_cols,chunk", [
+    (4, 3, 300, 57_401, 1024),      # four column quads a lane, a ragged last chunk
+    (4, 1, 300, 30_001, 512),       # two: four would leave too few blocks
+    (4, 6, 45, 198_001, 512),       # two, of two replica quads
+    (4, 6, 300, 57_401, 256),       # one: too few slabs for two
+    (8, 3, 300, 57_401, 512),       # bytes: two column quads a lane at most
+    (8, 6, 45, 198_001, 256),
+    (16, 2, 300, 57_402, 256),
+    (4, 6, 300, 4_099, None),       # a small launch: long and short items take different chunks
+    (8, 20, 300, 2_050, None),
+])
+def test_wide_chunks(bits, m, h, n_cols, chunk):
+    """Blocks that list one, two and four column quads per lane, by replica
+    quads, state format and blocks of the launch (asserted from the colours),
+    against the oracle."""
     rng = np.random.default_rng(m)
-    parents = [[] for _ in range(40)] + [[int(p) for p in sorted(rng.choice(40, 2, replace=False))] for _ in range(80)]
-    net, st, ob, th = _custom(parents, [2] * 120, n_cols, m, 0.3, 5)
-    ctx = H.context_for(net)
+    parents = [[] for _ in range(h)] + [[int(rng.integers(h if chunk else 5))] for _ in range(h)]
+    if chunk is None:          # five roots of many children beside the childless
+        parents = [[] for _ in range(h // 2)] + parents[h:h + h // 2]
+    card = [2] * len(parents)
+    if bits == 16:
+        parents, card = parents + [[]], card + [130]
+    net, st, ob, th = _custom(parents, card, n_cols, m, 0.3, 5)
+    ctx = H.context_for(net, state_bits=4 if bits == 4 else 0)
     color = oracle.graph(net.parents, net.card)["color"]
+    counts = np.bincount(color[:len(parents) - (bits == 16)])
+    assert [_sweep_chunk(c, m, n_cols, bits // 2) for c in counts] == [chunk] * 2
+    if chunk is None:          # the roots of many children share their colour with short items
+        kids = np.bincount([p[0] for p in parents if p], minlength=len(parents))
+        assert kids[:5].min() > 8 and (kids[color == color[0]] == 0).any()
     gpu, _ = H.gpu_sweep(ctx, st, ob, th, m, n_cols, 0, 5, 1)
     ref = st.copy()
     res = oracle.sweep(net.parents, net.card, th, color, ref, ob, m, n_cols, 0, 5, 1, want_flags=True)
