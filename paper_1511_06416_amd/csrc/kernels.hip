@@ -516,6 +516,7 @@ constexpr uint32_t kXcds = 8;
 constexpr int kSweepPasses = 4;  // most column quads per lane that a sweep block lists
 constexpr int kMinSweepBlocks = 4096;  // replicas are split below this many blocks
 constexpr int kTinyWaves = 2048;       // small networks: waves of a launch before a wave takes more columns
+constexpr int kMinLongBlocks = 768;    // least blocks of a small launch's long items
 constexpr int kMinLightBlocks = 512;   // the same for the short items of a small launch: chunks ...
 constexpr int kMinLightSplit = 768;    // ... and replicas
 constexpr int64_t kMinSweepQuads = 64;  // narrowest column chunk of a sweep block (quads)
@@ -3102,14 +3103,26 @@ hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_l
     const bool small = count * chunks_of(block_quads) * m_quads < dev::kMinSweepBlocks;
     int n_geom = 1;
     if (klass == 0 && small) {
-        // a small launch: long items in the narrowest chunks that fill the
+        // A small launch: long items in the narrowest chunks that fill the
         // device, the others in wide ones.  A block of one short item per
         // lane is nearly all start; one of several long ones per lane is the
         // launch's tail.  Six launches of 30 concepts (20 groups) and 300
         // items over 4000 columns, m = 20: 17-21 us each with every node in
-        // 256-column chunks (1024-column chunks: over 50), 11-13 us so.
-        if (n_long > 0) P.geom[0] = geometry(begin, n_long, block_quads, dev::kMinSweepQuads, dev::kMinSweepBlocks,
-                                                 dev::kMinSweepBlocks);
+        // 256-column chunks (1024-column chunks: over 50), 11-13 us so.  The
+        // long items' share of the whole launch's blocks is enough, at least
+        // kMinLongBlocks: asking for all of them from the long items alone
+        // halves their chunks once more (200 nodes of 2 to 8 states x 23,252
+        // columns, m = 12: 184 us per step, 156 with the share; one geometry
+        // for all 175); without the least number 6 concepts x 16,000 columns,
+        // m = 20, take 64 us (59).  Over 233 steps of 20 to 330 nodes, 500 to
+        // 200,000 columns, m = 1 to 20, mean time against one geometry:
+        // 0.833; with 256 / 384 as the short items' least blocks 0.837, with
+        // 1024 / 1536 0.848; with items long from a cost of 8 or 32 on 0.839
+        // and 0.848 (16: kLongItem).
+        const int64_t share = (int64_t)dev::kMinSweepBlocks * n_long / count;
+        const int64_t long_blocks = share > dev::kMinLongBlocks ? share : dev::kMinLongBlocks;
+        if (n_long > 0)
+            P.geom[0] = geometry(begin, n_long, block_quads, dev::kMinSweepQuads, long_blocks, long_blocks);
         if (n_long < count)
             P.geom[n_long > 0 ? 1 : 0] =
                 geometry(begin + n_long, count - n_long, block_quads, dev::kMinSweepQuads, dev::kMinLightBlocks,
