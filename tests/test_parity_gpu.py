@@ -226,19 +226,27 @@ def test_many_group_nodes(bits, lds):
     _custom_case(net, st, ob, th, 6, 1000, win=(0, 64), table_limit=0, **kw)
 
 
-@pytest.mark.parametrize("n_kids,n_par", [(4, 0), (5, 1), (8, 1), (9, 2), (7, 3), (12, 4)])
+@pytest.mark.parametrize("n_kids,n_par,last,entries", [
+    (4, 0, 0, 2), (5, 1, 0, 2), (8, 1, 0, 2), (9, 2, 0, 2),
+    (7, 3, 0, 4),          # an own row of three entries
+    (6, 4, 0, 4),          # of four
+    (9, 3, 3, 4),          # a child's group of four (the child and three other parents)
+    (12, 4, 4, None),      # of five: no records
+    (5, 5, 0, None),       # an own row of five
+])
 @pytest.mark.parametrize("bits", [0, 4, 16])
-def test_group_records(n_kids, n_par, bits):
-    """Two-state product nodes with fixed-size group records: 4, 8 and 9 groups
-    after the root's own (batches of four with a rest), groups of at most two
-    entries and of up to four (an own row of three or four parents: batches of
-    two), and an own row of five parents, which has none."""
+def test_group_records(n_kids, n_par, last, entries, bits):
+    """Two-state product nodes with fixed-size group records of two and four
+    entries, short and full ones, in batches of four and of two groups with a
+    rest, and nodes whose largest group has five entries, which have none."""
     par = list(range(n_par))
     hub = n_par                     # the node under test
     parents = [[] for _ in par] + [par]
     for k in range(n_kids):         # children with the hub and at most one parent more
         parents.append([hub] if k % 2 or not par else [par[k % n_par], hub])
-    parents.append(par + [hub] if n_par == 4 else [hub])
+    parents.append(par[:last] + [hub])
+    most = max([n_par] + [len(p) for p in parents[hub + 1:]])  # a child's group: itself and its other parents
+    assert (None if most > 4 else 2 if most <= 2 else 4) == entries
     card = [2] * len(parents)
     if bits == 16:
         parents, card = parents + [[]], card + [130]
