@@ -65,7 +65,9 @@ enum SweepMode : int32_t {
 //   3 generic path (K > 16).
 constexpr int32_t kLaunchClasses = 4;
 constexpr int64_t kLdsBudgetBytes = 32768;   // largest LDS staging budget per block
-constexpr int64_t kDefaultLdsBytes = 24576;  // default budget: 6 blocks per CU (measured best)
+// default budget (measured best): 6 blocks per CU beside the 2 KB list of 1024
+// columns, 5 or 4 beside the 4 or 8 KB lists of launches with wider chunks
+constexpr int64_t kDefaultLdsBytes = 24576;
 // default threshold-table limit (entries): a table then fits the default LDS
 // budget, so no threshold node gathers from global memory (measured best)
 constexpr int64_t kDefaultTableLimit = kDefaultLdsBytes / 4;

@@ -1,12 +1,13 @@
 // gfx950 kernels of libsame: table build, colour-group Gibbs sweep, count
 // histogram, moving sum, Gamma/Dirichlet resample.
 //
-// Data layout (HBM): states [n][m][ld] int8 (or int16), obs [n][ld] uint8.
+// Data layout (HBM): states as replica quads [n][ceil(m / 4)][ld][4] of 4-bit,
+// int8 or int16 states (see Quad), obs [n][ld] uint8.
 // The fast sweep kernel works on items: one latent column of a node and a
 // quad of its replicas, whose four draws take the four words of one Philox
 // block; consecutive lanes take consecutive latent columns, so the state
-// loads of a wavefront fall in a few cache lines per replica row.  The count
-// and ingest kernels read whole column quads (dwords) per lane.
+// loads of a wavefront fall in a few cache lines per quad row.  The count
+// kernel reads eight adjacent columns' quads per lane.
 #include <hip/hip_runtime.h>
 #include <type_traits>
 
@@ -762,7 +763,7 @@ __device__ __forceinline__ void item_product_flat(cint32_t *f, lds_char *lds, gl
 // in flight together, and the next groups' while these are multiplied; then
 // all their k-vectors are read, then multiplied in list order.  The weights
 // start at one (exact).  Nothing depends on an entry's flags, so a batch is
-// straight-line code.  (The flat walk below waits for a scalar load and
+// straight-line code.  (The flat walk above waits for a scalar load and
 // branches at every entry: about 11 us for the 40 entries of a concept with 20
 // items, when few waves are resident; 6 us so.)
 constexpr int kRecordLoads = 8;
@@ -1875,6 +1876,12 @@ constexpr int kCountQuads = 3;  // replica quads whose rows are loaded together 
 // are counted with packed 16-bit arithmetic (two lanes per word, as in the
 // sweep) when the node has at most 2^16 bins, else with 32-bit indices.
 // Padding slots (replicas >= m) and columns past the slab are not counted.
+//
+// Waves per SIMD: 5 for 4-bit states (96 registers, one spilled; 23 in the
+// copy with narrow accesses), 4 for bytes and 2 for 16-bit states (115 and 130
+// registers).  The bound hardly matters: over 12 networks and sizes 4 waves for
+// 4-bit states take 0.996 of the time (three quads and more 1.004), 5 for
+// bytes 1.006, 1 for 16-bit states 1.001.
 template <typename ST, bool WIDE>
 __global__ __launch_bounds__(kBlock, Quad<ST>::kBytes == 2 ? 5 : Quad<ST>::kBytes == 4 ? 4 : 2) void count_kernel(const int32_t *__restrict__ cdesc,
                                                       const int32_t *__restrict__ cdesc_off,
@@ -1982,6 +1989,10 @@ __global__ __launch_bounds__(kBlock, Quad<ST>::kBytes == 2 ? 5 : Quad<ST>::kByte
             // straight and all their loads are in flight together
             auto quads = [&](auto nt, int rq0) {
                 constexpr int NT = decltype(nt)::value;
+                // the next parent's rows loaded one ahead where the registers
+                // hold them: over 12 networks and sizes the pass takes 1.03 of
+                // the time without (4-bit states), 1.01 (bytes), and with them
+                // for three quads of 16-bit states too 1.23
                 constexpr bool kAhead = Quad<ST>::kBytes == 2 || NT < kCountQuads;
                 uint32_t boff[NT];
                 S own[NT];
