@@ -2366,7 +2366,7 @@ constexpr int kResampleBlock = kResampleTile;
 struct ResampleShared {
     double gam[kResampleBlock], shape[kResampleBlock], sums[kResampleBlock];
     uint16_t row_of_entry[kResampleBlock], list[kResampleBlock];
-    int32_t n_list;
+    int32_t n_list, boost;  // boost: some shape is below one
 };
 
 template <typename T, bool MOVING>
@@ -2377,7 +2377,7 @@ __device__ __forceinline__ void resample_draws(ResampleShared &S, int64_t base, 
 #pragma clang fp contract(off)
     const int tid = (int)threadIdx.x;
     const int64_t e = base + tid;
-    if (tid == 0) S.n_list = 0;
+    if (tid == 0) S.n_list = S.boost = 0;
     __syncthreads();
     if (tid < n_e) {
         double a;
@@ -2399,6 +2399,7 @@ __device__ __forceinline__ void resample_draws(ResampleShared &S, int64_t base, 
             done = y.v > 0.0 && y.ua < 1.0 - 0.0331 * (z2 * z2);
             S.gam[tid] = d * (y.v * y.v * y.v);
         }
+        if (a < 1.0) S.boost = 1;
         if (!done) {
             S.shape[tid] = a;
             S.list[atomicAdd(&S.n_list, 1)] = (uint16_t)tid;
@@ -2412,11 +2413,12 @@ __device__ __forceinline__ void resample_draws(ResampleShared &S, int64_t base, 
         S.gam[x] = gamma_mt(S.shape[x], (uint32_t)(base + x), u, k0, k1, ub);
         S.sums[x] = ub;
     }
-    // the boost of shapes below one (all of them listed, each by this lane)
-    for (int l = tid; l < n_list; l += kResampleBlock) {
-        const int x = S.list[l];
-        const double a = S.shape[x];
-        if (a < 1.0) S.gam[x] *= pow(S.sums[x], 1.0 / a);
+    if (S.boost) {  // shapes below one (all of them listed, each by this lane)
+        for (int l = tid; l < n_list; l += kResampleBlock) {
+            const int x = S.list[l];
+            const double a = S.shape[x];
+            if (a < 1.0) S.gam[x] *= pow(S.sums[x], 1.0 / a);
+        }
     }
     __syncthreads();
 }
