@@ -277,8 +277,8 @@ int same_sample_cpts(same_ctx *ctx, const int32_t *totals, float *cpts_out, uint
  * column-tile width and the number of sweep-kernel launches per call (for
  * profiling; host only): per tile one for each launch class of each colour
  * group, or a single one for all colours of a small network (few nodes, all on
- * threshold tables, and few replicas), which same_step makes do its counts
- * too.
+ * threshold tables, and few replicas; for some the columns count too), which
+ * same_step makes do its counts too.
  */
 int same_sweep_plan(const same_ctx *ctx, int32_t m, int64_t n_cols, int64_t *tile_cols,
                     int32_t *launches);

@@ -339,7 +339,7 @@ int sweep_tile(same_ctx *ctx, const same::DeviceTables &t, const same::SweepPara
     P.col_offset = P0.col_offset + t0;
     P.win_begin = P0.win_begin - t0;
     if (counted) *counted = false;
-    if (P.win == 0 && same::tiny_network(g, P.m)) {
+    if (P.win == 0 && same::tiny_network(g, P.m, nt)) {
         if (counted) *counted = counts != nullptr;
         // timed as one class-0 launch and one colour phase
         KernelTiming::Rec phase{-1, 1, nullptr, nullptr, 0.0};
@@ -713,8 +713,8 @@ int same_sweep_plan(const same_ctx *ctx, int32_t m, int64_t n_cols, int64_t *til
     same_layout(ctx, &lay, nullptr, nullptr);
     *tile_cols_out = T;
     // a small network's colours are one launch per tile
-    const int32_t per_tile = same::tiny_network(ctx->g, m) ? 1 : lay.sweep_launches;
-    *launches = (int32_t)(((n_cols + T - 1) / T) * per_tile);
+    auto per_tile = [&](int64_t cols) { return same::tiny_network(ctx->g, m, cols) ? 1 : lay.sweep_launches; };
+    *launches = (int32_t)(n_cols / T * per_tile(T) + (n_cols % T ? per_tile(n_cols % T) : 0));
     return SAME_OK;
 }
 

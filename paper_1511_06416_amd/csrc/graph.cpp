@@ -572,7 +572,7 @@ int compile_graph(int32_t n, const int32_t *pptr, const int32_t *pidx, const int
         }
     }
 
-    g.tiny = n <= kTinyNodes && n <= 2 * g.n_colors && g.off[n] <= kTinyBins && g.cond_words <= kTinyCondWords;
+    g.tiny = n <= kTinyWideNodes && g.off[n] <= kTinyBins && g.cond_words <= kTinyCondWords;
     for (int32_t i = 0; i < n; ++i)
         g.tiny = g.tiny && g.mode[i] == kModeTable && g.klass[i] == 0;
 

@@ -78,19 +78,27 @@ constexpr int32_t kDescHeader = 16;
 // than more items per lane
 constexpr int64_t kLongItem = 16;
 // A small network (tiny_step_kernel): every node draws from a staged threshold
-// table, with at most kTinyNodes nodes, two per colour group, kTinyBins CPT
-// entries (the histogram's 32 copies take 8 KB) and kTinyCondWords threshold
-// words; a wave's columns of all nodes and replicas take at most
-// kTinyWaveBytes.  The one launch chains the nodes (1.7 us each at 2,000
+// table, with at most kTinyBins CPT entries (the histogram's 32 copies take 8
+// KB) and kTinyCondWords threshold words; a wave's columns of all nodes and
+// replicas take at most kTinyWaveBytes; and at most kTinyNodes nodes, two per
+// colour group, or kTinyWideNodes of kTinyWideBins entries for one replica quad
+// of kTinyWideCols columns and more (tiny_network).  The one launch chains the nodes (1.7 us each at 2,000
 // columns), launches per colour group chain the groups: a step of a chain of 6
 // nodes (2 groups) takes 22.0 us with one launch and 22.2 with three, of 6
 // nodes in 3 groups 23.8 and 25.6, of a chain of 10 nodes 29 and 21, of 24
 // nodes 52 and 22; at a million columns, m = 10: 6 nodes in 3 groups 104 and
 // 106 us, a chain of 10 nodes 167 and 110.  More CPT entries leave fewer
 // blocks a CU: 5 nodes of 80 entries, a million columns, m = 10, 128 and 96
-// us, of 34 entries 94 and 88.
+// us, of 34 entries 94 and 88.  With one quad and many columns the launch reads
+// the states once where the others re-read them: a chain of 6 nodes, m = 4,
+// 530,000 columns 50 and 48 us, a million 59 and 71, two million 91 and 115; of
+// 8 nodes 62 and 53, 74 and 77, 116 and 125; 8 nodes in 3 groups with 38
+// entries and bytes, a million, 99 and 81.
 constexpr int32_t kTinyNodes = 6;
 constexpr int64_t kTinyBins = 64;
+constexpr int32_t kTinyWideNodes = 8;
+constexpr int64_t kTinyWideCols = 917504;  // 3584 waves of 256 columns
+constexpr int64_t kTinyWideBins = 32;
 constexpr int64_t kTinyCondWords = 2048;
 constexpr int64_t kTinyWaveBytes = 8192;
 constexpr int32_t kRecordGroups = 4;         // fewest groups that get records (see the descriptor)

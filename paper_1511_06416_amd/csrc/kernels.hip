@@ -3177,10 +3177,12 @@ hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_l
     return hipGetLastError();
 }
 
-bool tiny_network(const Compiled &g, int32_t m) {
+bool tiny_network(const Compiled &g, int32_t m, int64_t n_cols) {
     if (!g.tiny) return false;
     const int64_t mq = ((int64_t)m + 3) / 4;
-    return g.n * mq * 64 * g.quad_bytes <= kTinyWaveBytes;
+    if (g.n * mq * 64 * g.quad_bytes > kTinyWaveBytes) return false;
+    return (g.n <= kTinyNodes && g.n <= 2 * g.n_colors) ||
+           (mq == 1 && n_cols >= kTinyWideCols && g.off[g.n] <= kTinyWideBins);
 }
 
 hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, int32_t *counts,

@@ -89,10 +89,10 @@ hipError_t launch_prepare(const DeviceTables &t, const float *cpts, float *table
 hipError_t launch_sweep(SweepParams P, int32_t begin, int32_t count, int32_t n_long, int32_t klass,
                         int32_t lds_bytes, int32_t state_bits, hipStream_t stream);
 
-// Whether a network swept with m replicas takes the one-launch kernel of small
-// networks, and that launch: all colours over the columns of P and, with
-// counts, the family histograms (added to counts).
-bool tiny_network(const Compiled &g, int32_t m);
+// Whether a network takes the one-launch kernel of small networks for a sweep of
+// n_cols columns with m replicas, and that launch: all colours over the columns
+// of P and, with counts, the family histograms (added to counts).
+bool tiny_network(const Compiled &g, int32_t m, int64_t n_cols);
 hipError_t launch_tiny(SweepParams P, const DeviceTables &t, const Compiled &g, int32_t *counts, hipStream_t stream);
 
 hipError_t launch_fill_zero(int32_t *p, int64_t count, hipStream_t stream);

@@ -268,6 +268,8 @@ def test_sweep_plan_launches():
     ([[], [0], [1], [2]], [2] * 4, True),                              # four in two
     ([[], [0], [0, 1], [2], [2], [3]], [2, 3, 2, 4, 2, 2], True),      # six in three
     ([[], [0], [0, 1], [2], [2], [3], [3]], [2] * 7, False),           # seven nodes
+    ([[i - 1] if i else [] for i in range(8)], [2] * 8, False),
+    ([[i - 1] if i else [] for i in range(9)], [2] * 9, False),
     ([[], [], []], [2] * 3, False),                                    # three nodes in one group
     ([[], [0], [0, 1]], [4, 4, 4], False),                             # 84 CPT entries
     ([[i - 1] if i else [] for i in range(24)], [2] * 24, False),
@@ -280,6 +282,11 @@ def test_small_network_rule(parents, card, one):
     ctx = same.same_create(pptr, pidx, np.array(card, np.int32))
     assert ctx.table_nodes == len(card)
     assert same.same_sweep_plan(ctx, 4, 2_000)[1] == (1 if one else ctx.n_colors)
+    # more nodes per group: with one replica quad of many columns and few entries
+    wide = one or (len(card) <= 8 and ctx.cpt_total <= 32)
+    assert same.same_sweep_plan(ctx, 4, 917_504)[1] == (1 if wide else ctx.n_colors)
+    assert same.same_sweep_plan(ctx, 4, 917_503)[1] == (1 if one else ctx.n_colors)
+    assert same.same_sweep_plan(ctx, 5, 917_504)[1] == (1 if one else ctx.n_colors)
 
 
 def test_kernel_timing_host_calls():

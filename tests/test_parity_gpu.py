@@ -317,6 +317,7 @@ def _small_network_geometry(n, quad_bytes, m, n_cols):
 STUDENT = [[], [], [0], [0, 1], [3]], [2, 2, 2, 3, 2]
 SIX = [[], [0], [0, 1], [2], [2], [3]], [2, 3, 2, 4, 2, 2]
 PAIR = [[], [0]], [9, 5]             # eight thresholds per configuration
+CHAIN = [[]] + [[i] for i in range(7)], [2] * 8   # four nodes per colour group
 
 
 @pytest.mark.parametrize("net,n_cols,m,geometry", [
@@ -332,6 +333,7 @@ PAIR = [[], [0]], [9, 5]             # eight thresholds per configuration
     (STUDENT, 262_209, 10, (2, 3, 3)),     # 128 columns a wave
     (SIX, 270_001, 6, (2, 2, 2)),
     (STUDENT, 600_001, 2, (4, 1, 1)),      # 256 columns
+    (CHAIN, 920_001, 3, (4, 1, 1)),        # one quad of many columns
     (STUDENT, 530_001, 5, None),           # 256 columns in 4 bits, 128 in bytes
     (STUDENT, 200, 200, None),             # too many replicas for a wave: the colour launches
 ])
